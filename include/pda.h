@@ -363,9 +363,12 @@ typedef struct pda_prefill_problem {
  *
  * Query token i of sequence b sits at position L_b - n_b + i and attends to
  * tokens 0 .. L_b - n_b + i of its sequence (softmax_scale on the logits, KV
- * head h / G); a token at a negative position (n_b > L_b) gets zeros. Every
- * output row is computed by one workgroup with no split of the keys, so the
- * result does not depend on the launch order.
+ * head h / G); a token at a negative position (n_b > L_b) gets zeros. A call
+ * with few query tiles splits a long tile's keys over several workgroups, by a
+ * plan made from q_offsets and seq_lens alone, and merges their partial results
+ * in key order, so the result does not depend on the launch order. (A capture
+ * into a HIP graph, or a failed allocation, that leaves no room for the partials
+ * runs without the split; its results differ by the rounding of the merge.)
  *
  * Precision: q . k in bf16 products with fp32 sums; the softmax weights (at
  * most 2^8 after the running-max shift) and V (fp8: code times V scale) enter
@@ -392,8 +395,9 @@ typedef struct pda_prefill_problem {
  * 16 bytes, the int32 and f32 arrays 4), or more than INT32_MAX / 8 work units
  * (tiles of 256 / G query tokens times KV heads); PDA_EUNSUPPORTED for
  * head_dim not in {64, 128}, block_size != 16, G > 16, or an f32 cache. Uses
- * the stream's workspace: 16 bytes per work item of 256 / G query tokens, plus
- * the image described above.
+ * the stream's workspace: 16 bytes per work item of 256 / G query tokens, the
+ * partials of a split (256 * (4 head_dim + 8) bytes per part, at most about two
+ * parts per compute unit: 68 MB), and the image described above.
  */
 int pda_paged_prefill_attention(const void* q,
                                 const int32_t* q_offsets,

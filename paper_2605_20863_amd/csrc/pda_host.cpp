@@ -656,26 +656,47 @@ int prefill_run(const void* q, const int32_t* q_offsets, const void* k_cache, co
   if (!di.ok) return fail(PDA_EUNSUPPORTED, "device %d is %s; this library is built for gfx950", dev, di.arch.c_str());
   Workspace* ws = workspace_for(dev, stream);
   std::lock_guard<std::mutex> lk(ws->mu);
+  const int len_cap = pr->max_seq_len > 0 ? pr->max_seq_len : (int)table_tokens;
+  // Workspace: header, work items, and as room and caps allow the split plan's
+  // partials and the image. A capture that cannot grow the workspace, or a
+  // failed allocation, goes without the image (the staging kernel's results
+  // are the same), then without the split.
   const int64_t items_off = align_up(pda::kHdrWords * 4);
+  // A KV head's partial slots: a tile split into items of at least the grid's
+  // even share has at most twice its pairs over that share of them, so a call
+  // has at most 2 * wgs / Hkv, and never more than every tile cut to the
+  // fewest pairs. No split where the longest cache has no room for one.
+  const int64_t most_cut = ((int64_t)len_cap / 32 + 1 + pda::kPfSplitPairs - 1) / pda::kPfSplitPairs;
+  int64_t slots = 2 * (((int64_t)di.cus + pr->num_kv_heads - 1) / pr->num_kv_heads) + 2;
+  if (slots > items_max * most_cut) slots = items_max * most_cut;
+  if (items_max * pr->num_kv_heads > (int64_t)pda::kPfSplitUnits * di.cus || items_max > pda::kPfSplitTiles ||
+      pr->num_seqs > pda::kPfSplitSeqs || most_cut < 2)
+    slots = 0;
+  const int64_t cols = slots * pr->num_kv_heads * pda::kPfColumns;
+  const int64_t list_max = items_max + slots;  // a split adds at most its slots
   const int64_t plain_bytes = items_off + items_max * 16;
-  // The image (V in fp16; for an fp8 cache K in bf16 too) follows the work
-  // list when it fits the cap; a capture that cannot grow the workspace, or a
-  // failed allocation, takes the staging kernel, whose results are the same.
+  const int64_t parts_off = items_off + list_max * 16;
+  const int64_t splits_off = align_up(parts_off + list_max * 16);
+  const int64_t ml_off = align_up(splits_off + slots / 2 * 16);
+  const int64_t acc_off = align_up(ml_off + cols * 8);
+  const int64_t split_bytes = acc_off + cols * pr->head_dim * 4;
+  // Image: V in fp16; for an fp8 cache K in bf16 too.
   const int64_t img_half = pr->num_blocks * pr->num_kv_heads * (int64_t)pda::kBlockSize * pr->head_dim * 2;
   const int64_t img_bytes = kd == PDA_DTYPE_FP8_E4M3 ? 2 * img_half : img_half;
-  const int64_t img_off = align_up(plain_bytes);
+  const bool cap = capturing(stream);
   bool use_img = img_bytes <= prefill_image_cap();
-  if (use_img && capturing(stream) && ws->bytes < img_off + img_bytes) use_img = false;
-  if (use_img) {
-    rc = ensure_workspace(ws, img_off + img_bytes, stream);
-    if (rc == PDA_ENOMEM) {
-      use_img = false;
-      g_error.clear();
-    } else if (rc != PDA_OK) {
-      return rc;
-    }
+  int64_t base_bytes = slots ? split_bytes : plain_bytes;
+  if (cap && ws->bytes < base_bytes) slots = 0, base_bytes = plain_bytes;
+  if (use_img && cap && ws->bytes < align_up(base_bytes) + img_bytes) use_img = false;
+  for (;;) {
+    rc = ensure_workspace(ws, use_img ? align_up(base_bytes) + img_bytes : base_bytes, stream);
+    if (rc != PDA_ENOMEM || !(use_img || slots)) break;
+    if (use_img) use_img = false;
+    else slots = 0, base_bytes = plain_bytes;
+    g_error.clear();
   }
-  if (!use_img && (rc = ensure_workspace(ws, plain_bytes, stream)) != PDA_OK) return rc;
+  if (rc != PDA_OK) return rc;
+  const int64_t img_off = align_up(base_bytes);
   char* base = static_cast<char*>(ws->ptr);
 
   pda::PrefillArgs a;
@@ -698,7 +719,7 @@ int prefill_run(const void* q, const int32_t* q_offsets, const void* k_cache, co
   a.TQ = TQ;
   a.max_blocks = pr->max_blocks_per_seq;
   a.num_blocks = pr->num_blocks;
-  a.len_cap = pr->max_seq_len > 0 ? pr->max_seq_len : (int)table_tokens;
+  a.len_cap = len_cap;
   int shift = 0;
   while ((a.len_cap >> shift) >= pda::kPfBuckets) ++shift;
   a.len_shift = shift;
@@ -708,6 +729,12 @@ int prefill_run(const void* q, const int32_t* q_offsets, const void* k_cache, co
   a.nq = std::gcd(a.Hkv, 8);
   a.hdr = reinterpret_cast<int32_t*>(base);
   a.items = reinterpret_cast<int4*>(base + items_off);
+  a.slots = (int32_t)slots;
+  a.wgs = 0;  // the launcher's
+  a.parts = reinterpret_cast<int4*>(base + parts_off);
+  a.splits = reinterpret_cast<int4*>(base + splits_off);
+  a.part_ml = reinterpret_cast<float2*>(base + ml_off);
+  a.part_acc = reinterpret_cast<float*>(base + acc_off);
   a.v_img = use_img ? base + img_off : nullptr;
   a.k_img = use_img && kd == PDA_DTYPE_FP8_E4M3 ? base + img_off + img_half : nullptr;
   const pda::KvType kv = kd == PDA_DTYPE_BF16 ? pda::KvType::BF16 : pda::KvType::FP8;

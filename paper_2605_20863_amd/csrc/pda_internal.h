@@ -37,6 +37,7 @@ constexpr int kHdrStatus = 0;
 constexpr int kHdrShare = 1;  // block-heads per chunk (decode writes, combine reads)
 constexpr int kHdrNext = 2;   // chunk counter of a dynamic split; zero between calls
 constexpr int kHdrItems = 3;  // prefill: work items the plan kernel listed
+constexpr int kHdrSplits = 4; // prefill: tiles whose keys the plan split over several items
 constexpr int kHdrPfQueue = 8;  // prefill: words 8..15, the unit counters of the attention grid's queues
 constexpr int kHdrWords = 16;
 
@@ -115,6 +116,14 @@ hipError_t launch_append(const AppendArgs& a, KvType kv, hipStream_t s);
 // Variable-length causal prefill (pda_prefill.hip).
 constexpr int kPfColumns = 256;  // query (token, head) columns per workgroup
 constexpr int kPfBuckets = 2048; // length classes of the plan's counting sort
+// A call of at most kPfSplitUnits units (tiles x KV heads) per compute unit is
+// planned with its keys split where the tiles alone leave compute units idle;
+// with more units the queues even them out, and the kernel without the split is
+// a few percent faster per pair.
+constexpr int kPfSplitUnits = 8;
+constexpr int kPfSplitTiles = 2048;
+constexpr int kPfSplitSeqs = 1024;
+constexpr int kPfSplitPairs = 16;  // fewest 32-key pairs a split makes per item
 
 struct PrefillArgs {
   const void* q;        // [T, Hq, D] bf16
@@ -138,7 +147,19 @@ struct PrefillArgs {
   int32_t cus;          // compute units of the device
   int32_t nq;           // unit queues: gcd(Hkv, 8)
   int32_t* hdr;         // workspace header (status, item count, queue counters)
-  int4* items;          // [items_max] {sequence, first q row, tokens, first position}
+  int4* items;          // [items_max + slots] {sequence, first q row, tokens, first position}
+  // Split plan (slots > 0): every item also has an entry in `parts` {first
+  // 32-key pair, end pair, partial slot or -1, 0}. A tile whose keys are split
+  // over several items has one slot per item and an entry in `splits` {first q
+  // row, tokens, first slot, slots}; each of its items writes its unnormalised
+  // output and softmax state to its slot (per KV head and column), and the
+  // merge kernel combines them. slots bounds the slots of one KV head.
+  int32_t slots;
+  int32_t wgs;          // workgroups of the attention grid
+  int4* parts;          // [items_max + slots]
+  int4* splits;         // [slots / 2]
+  float2* part_ml;      // [slots, Hkv, kPfColumns] running max (base 2), denominator
+  float* part_acc;      // [slots, Hkv, kPfColumns, D]
   // Image of the cache's tiles in the products' operand types, indexed like the
   // cache (block * Hkv + KV head, 16 * D two-byte elements per tile): V in fp16
   // (v_img), and for an fp8 cache K in bf16 (k_img). v_img null: the attention

@@ -17,6 +17,13 @@
 //   every tile of a block that a sequence with queries reads, converted to the
 //   operand types of the products (V to fp16, fp8 as code times the block's V
 //   scale; for fp8 caches K codes to bf16), indexed like the cache.
+// * Split plan. Where the tiles alone leave compute units idle (a chunk of one
+//   long prompt: 15 tiles x 4 KV heads on 256 CUs, each walking 16k keys), the
+//   plan cuts a tile's keys into several items; each writes its unnormalised
+//   output and softmax state, and a merge kernel combines them. Measured, 512
+//   tokens over 16,182 cached ones, 28 / 4 heads, bf16: 462 us per call whole,
+//   164 us split (prep 18, attention 130, merge 8); 64-token turns of 16
+//   sequences over an fp8 cache, 32 / 8 heads: 234 against 178.
 // * Attention kernel: a persistent grid, one workgroup (8 waves, 2 per SIMD)
 //   per CU, that takes (item, KV head) units from queues, so a CU goes from one
 //   unit to the next without a workgroup launch between them (which cost ~4 us
@@ -60,7 +67,6 @@
 
 #include <stdint.h>
 
-#include <atomic>
 #include <type_traits>
 
 namespace pda {
@@ -150,16 +156,59 @@ __device__ PfSeq pf_seq(const PrefillArgs& a, int b, int& status, bool& bad) {
   return s;
 }
 
+struct PfPlanLds {
+  int cursor[kPfBuckets];
+  int wave_sum[kPlanThreads / 64];
+  // split plan only: each sequence's first q row, queries and length; each
+  // tile's sequence, index in it and pairs; sums
+  int q0[kPfSplitSeqs], n[kPfSplitSeqs], L[kPfSplitSeqs];
+  int tile_b[kPfSplitTiles], tile_t[kPfSplitTiles], tile_p[kPfSplitTiles];
+  unsigned long long pairs;
+  int tiles, longest, nsplits, nslots;
+  int count[kPlanThreads / 64];
+};
+
+// Exclusive scan of the per-bucket item counts in cursor: bucket starts in the
+// list; the total goes to the workspace header.
+__device__ __forceinline__ void pf_bucket_starts(const PrefillArgs& a, PfPlanLds& s) {
+  const int tid = (int)threadIdx.x;
+  constexpr int PER = kPfBuckets / kPlanThreads;
+  int v[PER], run = 0;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    v[i] = s.cursor[tid * PER + i];
+    run += v[i];
+  }
+  int x = run;
+  const int l = lane_id();
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o, 64);
+    if (l >= o) x += y;
+  }
+  if (l == 63) s.wave_sum[tid >> 6] = x;
+  __syncthreads();
+  int before = 0;
+  for (int w = 0; w < (tid >> 6); ++w) before += s.wave_sum[w];
+  int start = before + x - run;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    s.cursor[tid * PER + i] = start;
+    start += v[i];
+  }
+  if (tid == kPlanThreads - 1) a.hdr[kHdrItems] = start;  // total items
+  __syncthreads();
+}
+
+// 32-key pairs of `keys` keys
+__device__ __forceinline__ int pf_pairs(int keys) { return keys > 0 ? (keys + 31) / 32 : 0; }
+
 // Offsets that are not non-decreasing within [0, T] list no item at all (status
 // bit 8): with them the sequences could overlap and overrun the list. Otherwise
-// the tiles add up to at most (T + B (TQ - 1)) / TQ = items_max.
-__device__ void pf_plan(const PrefillArgs& a) {
-  __shared__ int cursor[kPfBuckets];
-  __shared__ int wave_sum[kPlanThreads / 64];
+// the tiles add up to at most (T + B (TQ - 1)) / TQ.
+__device__ void pf_plan_tiles(const PrefillArgs& a, PfPlanLds& lds) {
+  int* const cursor = lds.cursor;
   const int tid = (int)threadIdx.x;
-  for (int i = tid; i < kPfBuckets; i += kPlanThreads) cursor[i] = 0;
-  if (tid < 8) a.hdr[kHdrPfQueue + tid] = 0;
-  __syncthreads();
   int status = 0;
   bool bad = false;
   for (int b = tid; b < a.B; b += kPlanThreads) {
@@ -173,33 +222,7 @@ __device__ void pf_plan(const PrefillArgs& a) {
     }
     return;
   }
-  // exclusive scan of the per-bucket tile counts: bucket starts in the list
-  constexpr int PER = kPfBuckets / kPlanThreads;
-  int v[PER], run = 0;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    v[i] = cursor[tid * PER + i];
-    run += v[i];
-  }
-  int x = run;
-  const int l = lane_id();
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o, 64);
-    if (l >= o) x += y;
-  }
-  if (l == 63) wave_sum[tid >> 6] = x;
-  __syncthreads();
-  int before = 0;
-  for (int w = 0; w < (tid >> 6); ++w) before += wave_sum[w];
-  int start = before + x - run;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    cursor[tid * PER + i] = start;
-    start += v[i];
-  }
-  if (tid == kPlanThreads - 1) a.hdr[kHdrItems] = start;  // total items
-  __syncthreads();
+  pf_bucket_starts(a, lds);
   for (int b = tid; b < a.B; b += kPlanThreads) {
     const PfSeq s = pf_seq(a, b, status, bad);
     if (!s.tiles) continue;
@@ -211,6 +234,166 @@ __device__ void pf_plan(const PrefillArgs& a) {
     }
   }
   if (status) atomicOr(a.hdr + kHdrStatus, status);
+}
+
+// Split plan, for calls of few units: one 512-token chunk of a 7B-shaped model
+// is 60 units, and one long sequence among short ones keeps its units running
+// long after the others. A tile's pairs are split into
+// items of at most S pairs, a multiple of 4 (an item starts on the first LDS
+// buffer) and never below the grid's even share, so that a KV head's split items
+// stay below 2 * wgs / Hkv.
+//
+// S comes from an estimate of the call's time in pairs (about 0.94 us each),
+// over the 16 candidates share * (1 + k / 16): a unit costs its pairs and about
+// 7 more (prologue and epilogue); if every unit gets a workgroup the call takes
+// as long as its longest unit, otherwise the even share, the units' fixed
+// costs and about half of the longest unit; a split adds the partials and the
+// merge kernel (about 8). The plan is one workgroup's chain of round trips and
+// barriers, 9 us; with the candidates counted by every thread instead of one
+// wave each it took 16.
+constexpr float kUnitPairs = 7.f, kMergePairs = 8.f;
+
+__device__ __forceinline__ float pf_estimate(const PrefillArgs& a, float share, int longest, int tiles) {
+  const float units = (float)tiles * (float)a.Hkv, wgs = (float)a.wgs;
+  if (units <= wgs) return (float)longest + kUnitPairs;
+  return fmaxf((float)longest, share) + kUnitPairs * units / wgs + 0.5f * (float)longest;
+}
+
+__device__ void pf_plan_split(const PrefillArgs& a, PfPlanLds& lds) {
+  const int tid = (int)threadIdx.x;
+  const int l = lane_id(), wave = tid >> 6;
+  if (tid == 0) {
+    lds.pairs = 0;
+    lds.tiles = lds.longest = lds.nsplits = lds.nslots = 0;
+  }
+  __syncthreads();
+  // the sequences and their places in the tile list (in any order: the list is sorted)
+  int status = 0;
+  bool bad = false;
+  int at = 0, tiles_b = 0;
+  static_assert(kPfSplitSeqs == kPlanThreads, "a thread per sequence");
+  if (tid < a.B) {
+    const PfSeq s = pf_seq(a, tid, status, bad);
+    lds.q0[tid] = s.q0;
+    lds.n[tid] = s.n;
+    lds.L[tid] = s.L;
+    tiles_b = s.tiles;
+    if (!bad && tiles_b) at = atomicAdd(&lds.tiles, tiles_b);
+  }
+  if (__syncthreads_or(bad)) {
+    if (tid == 0) {
+      a.hdr[kHdrItems] = 0;
+      a.hdr[kHdrSplits] = 0;
+      atomicOr(a.hdr + kHdrStatus, kStatusBadOffsets);
+    }
+    return;
+  }
+  const int tiles = lds.tiles;
+  // each wave lists its 64 sequences' tiles, 64 tiles of one sequence at a time
+  uint64_t todo = __ballot(tiles_b > 0);
+  unsigned long long pairs = 0;
+  int longest = 0;
+  while (todo) {
+    const int src = __builtin_ctzll(todo);
+    todo &= todo - 1;
+    const int b = (wave << 6) + src;
+    const int nb = __builtin_amdgcn_readlane(tiles_b, src), at0 = __builtin_amdgcn_readlane(at, src);
+    const int n = lds.n[b], L = lds.L[b];
+    for (int t = l; t < nb; t += 64) {
+      const int end = (t + 1) * a.TQ;
+      const int p = pf_pairs(L - n + (end < n ? end : n));
+      lds.tile_b[at0 + t] = b;
+      lds.tile_t[at0 + t] = t;
+      lds.tile_p[at0 + t] = p;
+      pairs += (unsigned)p;
+      longest = longest > p ? longest : p;
+    }
+  }
+  if (pairs) {
+    atomicAdd(&lds.pairs, pairs);
+    atomicMax(&lds.longest, longest);
+  }
+  __syncthreads();
+  longest = lds.longest;
+  // the even share of one workgroup, at least kPfSplitPairs and at most `longest`
+  const unsigned long long even = (lds.pairs * (unsigned)a.Hkv + (unsigned)a.wgs - 1) / (unsigned)a.wgs;
+  const int base = even < (unsigned)kPfSplitPairs ? kPfSplitPairs
+                   : even > (unsigned long long)longest ? longest : (int)even;
+  auto candidate = [&](int k) { return (base + base * k / 16 + 3) & ~3; };  // base < 2^26
+  int S = 0;  // pairs per item; 0: no tile is split
+  if (base < longest) {
+    // wave k counts candidate k's items (an estimate: a quotient may be off by one)
+    static_assert(kPlanThreads / 64 == 16, "a wave per candidate");
+    const float inv = __builtin_amdgcn_rcpf((float)candidate(wave));
+    int count = 0;
+    for (int i = l; i < tiles; i += 64) count += (int)fmaxf(__builtin_ceilf((float)lds.tile_p[i] * inv), 1.f);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) count += __shfl_xor(count, o, 64);
+    if (l == 0) lds.count[wave] = count;
+    __syncthreads();
+    // lane k estimates candidate k, lane 16 the tiles as they are
+    const int k = l < 16 ? l : 15;
+    const bool whole = l >= 16;
+    const int s = candidate(k);
+    float e = pf_estimate(a, (float)even, whole ? longest : s, whole ? tiles : lds.count[k]) +
+              (whole ? 0.f : kMergePairs);
+    if (!whole && s >= longest) e = 3e38f;
+    float best = e;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) best = fminf(best, __shfl_xor(best, o, 64));
+    const int win = __builtin_ctzll(__ballot(e == best));  // the same in every wave
+    S = win < 16 ? candidate(win) : 0;
+  }
+  // a tile's items: c of len pairs each (the last may be shorter)
+  auto cut = [&](int p, int& len) {
+    len = p;
+    if (S == 0 || p <= S) return 1;
+    const int c = (p + S - 1) / S;
+    len = ((p + c - 1) / c + 3) & ~3;
+    return (p + len - 1) / len;
+  };
+  auto key = [&](int len) {
+    const unsigned k = ((unsigned)len * 32u) >> a.len_shift;
+    return kPfBuckets - 1 - (int)(k < kPfBuckets - 1u ? k : kPfBuckets - 1u);
+  };
+  for (int i = tid; i < tiles; i += kPlanThreads) {
+    int len;
+    const int c = cut(lds.tile_p[i], len);
+    atomicAdd(&lds.cursor[key(len)], c);
+  }
+  __syncthreads();
+  pf_bucket_starts(a, lds);
+  for (int i = tid; i < tiles; i += kPlanThreads) {
+    const int p = lds.tile_p[i], b = lds.tile_b[i], t0 = lds.tile_t[i] * a.TQ;
+    const int n = lds.n[b], row0 = lds.q0[b] + t0;
+    const int nt = n - t0 < a.TQ ? n - t0 : a.TQ;
+    int len;
+    const int c = cut(p, len);
+    int pos = atomicAdd(&lds.cursor[key(len)], c);
+    int slot = -1;
+    if (c > 1) {
+      slot = atomicAdd(&lds.nslots, c);
+      a.splits[atomicAdd(&lds.nsplits, 1)] = make_int4(row0, nt, slot, c);
+    }
+    for (int j = 0; j < c; ++j, ++pos) {
+      const int end = (j + 1) * len;
+      a.items[pos] = make_int4(b, row0, nt, lds.L[b] - n + t0);
+      a.parts[pos] = make_int4(j * len, end < p ? end : p, slot < 0 ? -1 : slot + j, 0);
+    }
+  }
+  __syncthreads();
+  if (tid == 0) a.hdr[kHdrSplits] = lds.nsplits;
+  if (status) atomicOr(a.hdr + kHdrStatus, status);
+}
+
+__device__ void pf_plan(const PrefillArgs& a) {
+  __shared__ PfPlanLds lds;
+  const int tid = (int)threadIdx.x;
+  for (int i = tid; i < kPfBuckets; i += kPlanThreads) lds.cursor[i] = 0;
+  if (tid < 8) a.hdr[kHdrPfQueue + tid] = 0;
+  __syncthreads();
+  if (a.slots > 0) pf_plan_split(a, lds);
+  else pf_plan_tiles(a, lds);
 }
 
 // ------------------------------------------------------- layout and image
@@ -399,7 +582,7 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PrefillArgs 
 
 // The plan (workgroup 0) and the image (the others) in one launch.
 template <KvType KV, int D>
-__global__ __launch_bounds__(kPlanThreads) void prefill_prep_kernel(PrefillArgs a) {
+__global__ __launch_bounds__(kPlanThreads, 8) void prefill_prep_kernel(PrefillArgs a) {
   if (blockIdx.x == 0) {
     pf_plan(a);
     return;
@@ -801,8 +984,8 @@ __device__ __forceinline__ void pf_pv(PfOps<KV, D>& o, const f16x8 (&ph)[kPfNT],
   }
 }
 
-template <KvType KV, int D, bool IMG>
-__global__ __launch_bounds__(kPfThreads) void prefill_kernel(PrefillArgs a) {
+template <KvType KV, int D, bool IMG, bool SPLIT>
+__device__ __forceinline__ void pf_body(const PrefillArgs& a) {
   using C = PfCfg<KV, D>;
   __shared__ __attribute__((aligned(16))) uint8_t lds[4 * C::BUF];
   __shared__ int s_next[2];
@@ -833,6 +1016,8 @@ __global__ __launch_bounds__(kPfThreads) void prefill_kernel(PrefillArgs a) {
     int tick = 0;
     if (threadIdx.x == 0) tick = atomicAdd(a.hdr + kHdrPfQueue + q, 1);
     const int4 it = a.items[item];
+    int4 part = make_int4(0, 0, -1, 0);
+    if constexpr (SPLIT) part = a.parts[item];
     const int b = it.x, row0 = it.y, nt = it.z, first = it.w;
 
     // this wave's columns: column col = 32w + 16n + r is token col / G, head col % G
@@ -862,7 +1047,8 @@ __global__ __launch_bounds__(kPfThreads) void prefill_kernel(PrefillArgs a) {
     const int pos_hi = uni(first + tok_hi);
 
     const int nkeys = first + nt > 0 ? first + nt : 0;  // keys up to the tile's last position
-    const int npairs = uni((nkeys + 31) / 32);
+    // the item's pairs [p0, npairs); p0 is a multiple of 4
+    const int p0 = SPLIT ? uni(part.x) : 0, npairs = SPLIT ? uni(part.y) : uni((nkeys + 31) / 32);
     const int nblk = uni((nkeys + 15) / 16);
     // pairs this wave computes: those with a key at or before its last position
     const int wpairs = uni(!wave_on || pos_hi < 0 ? 0 : (pos_hi / 32 + 1 < npairs ? pos_hi / 32 + 1 : npairs));
@@ -914,22 +1100,23 @@ __global__ __launch_bounds__(kPfThreads) void prefill_kernel(PrefillArgs a) {
     PfIds ids;
     ids.q = -1;
     ids.id = 0;
-    ids.nxt = pf_id_load(row, l, nblk);  // chunk 0
-    pf_ids_advance(ids, row, 0, nblk);
+    ids.nxt = pf_id_load(row, 64 * (p0 >> 5) + l, nblk);  // the first pair's chunk
+    pf_ids_advance(ids, row, p0 >> 5, nblk);
     PfMeta m0{1.f, 1.f, 0}, m1{1.f, 1.f, 0};
     {
-      const PfPair pa = pf_pair<KV, IMG>(a, ids, 0, nblk, nkeys, kvh, status);
-      const PfPair pb = pf_pair<KV, IMG>(a, ids, npairs > 1 ? 2 : 0, nblk, nkeys, kvh, status);
+      const PfPair pa = pf_pair<KV, IMG>(a, ids, 2 * p0, nblk, nkeys, kvh, status);
+      const PfPair pb = pf_pair<KV, IMG>(a, ids, 2 * p0 + (npairs - p0 > 1 ? 2 : 0), nblk, nkeys, kvh, status);
       if constexpr (IMG) {
-        if (npairs > 0) pf_dma<KV, D>(kimg, vimg, pa.t0, pa.t1, pl, lds0);
-        if (npairs > 1) pf_dma<KV, D>(kimg, vimg, pb.t0, pb.t1, pl, lds0 + C::BUF);
+        if (npairs > p0) pf_dma<KV, D>(kimg, vimg, pa.t0, pa.t1, pl, lds0);
+        if (npairs - p0 > 1) pf_dma<KV, D>(kimg, vimg, pb.t0, pb.t1, pl, lds0 + C::BUF);
         pf_dma_wait();
-      } else if (npairs > 0) {  // both pairs' loads before either store: one round trip
+      } else if (npairs > p0) {  // both pairs' loads before either store: one round trip
         PfStage<KV, D> sa, sb;
         pf_load<KV, D>(sa, a, pa.t0, pa.t1);
         pf_load<KV, D>(sb, a, pb.t0, pb.t1);
         pf_store<KV, D>(sa, pf_vs(pa, 0), pf_vs(pa, 1), pa.live, lds, status);
-        if (npairs > 1) pf_store<KV, D>(sb, pf_vs(pb, 0), pf_vs(pb, 1), pb.live, lds + C::BUF, status);
+        if (npairs - p0 > 1)
+          pf_store<KV, D>(sb, pf_vs(pb, 0), pf_vs(pb, 1), pb.live, lds + C::BUF, status);
       }
       m0 = pf_meta(pa, a.scale_log2);
       m1 = pf_meta(pb, a.scale_log2);
@@ -945,7 +1132,7 @@ __global__ __launch_bounds__(kPfThreads) void prefill_kernel(PrefillArgs a) {
       s_next[k & 1] = code;
     }
     __syncthreads();
-    for (int j2 = 0; j2 < npairs; j2 += 2) {
+    for (int j2 = p0; j2 < npairs; j2 += 2) {
       // blocks 2ja .. 2jb + 1 lie in one chunk of 64 (2ja is a multiple of 4, or jb = ja)
       const int ja = j2 + 2 < npairs ? j2 + 2 : npairs - 1, jb = j2 + 3 < npairs ? j2 + 3 : npairs - 1;
       pf_ids_advance(ids, row, ja >> 5, nblk);
@@ -993,7 +1180,18 @@ __global__ __launch_bounds__(kPfThreads) void prefill_kernel(PrefillArgs a) {
       }
       __syncthreads();
     }
-    if (wave_on) {
+    const int slot = SPLIT ? uni(part.z) : -1;
+    if (SPLIT && slot >= 0) {  // part of a split tile: the unnormalised output and its softmax state
+      const int64_t col0 = ((int64_t)slot * a.Hkv + kvh) * kPfColumns + kPfWaveCols * w + r;
+#pragma unroll
+      for (int n = 0; n < kPfNT; ++n) {
+        if (tokq[n] < 0) continue;
+        float* o = a.part_acc + (col0 + 16 * n) * D + 4 * c;
+#pragma unroll
+        for (int m = 0; m < C::MT; ++m) *reinterpret_cast<f32x4*>(o + 16 * m) = acc[m][n];
+        if (c == 0) a.part_ml[col0 + 16 * n] = float2{rows[n].m, rows[n].l[0]};
+      }
+    } else if (wave_on) {
 #pragma unroll
       for (int n = 0; n < kPfNT; ++n) {
         const float lt = rows[n].l[0];
@@ -1020,15 +1218,92 @@ __global__ __launch_bounds__(kPfThreads) void prefill_kernel(PrefillArgs a) {
   if (status) atomicOr(a.hdr + kHdrStatus, status);  // error paths only
 }
 
+template <KvType KV, int D, bool IMG>
+__global__ __launch_bounds__(kPfThreads) void prefill_kernel(PrefillArgs a) {
+  pf_body<KV, D, IMG, false>(a);
+}
+
+template <KvType KV, int D, bool IMG>
+__global__ __launch_bounds__(kPfThreads) void prefill_split_kernel(PrefillArgs a) {
+  pf_body<KV, D, IMG, true>(a);
+}
+
+// Merge of the split tiles' partials: D / 4 threads per query column, 4 dims
+// each, walk the column's partials,
+//     out = sum_i 2^(m_i - M) acc_i / sum_i 2^(m_i - M) l_i,   M = max_i m_i,
+// in item order, so the result does not depend on the launch order. A column's
+// partials lie kPfColumns * Hkv rows apart; a thread has four in flight. Bound
+// by the reads (D * 4 bytes per column and partial): 31 MB in 8 us for the
+// 512-token chunk above.
+constexpr int kMergeThreads = 256;
+constexpr int kMergeBatch = 4;
+
+template <int D>
+__global__ __launch_bounds__(kMergeThreads) void prefill_merge_kernel(PrefillArgs a) {
+  constexpr int TPC = D / 4, COLS = kMergeThreads / TPC;  // threads per column, columns per workgroup
+  constexpr int CHUNKS = kPfColumns / COLS;
+  const int dl = (int)threadIdx.x % TPC;
+  const int64_t stride = (int64_t)a.Hkv * kPfColumns;  // columns from one slot to the next
+  const int total = a.hdr[kHdrSplits] * a.Hkv * CHUNKS;
+  for (int u = (int)blockIdx.x; u < total; u += (int)gridDim.x) {
+    const int sp = u / (a.Hkv * CHUNKS), rest = u - sp * a.Hkv * CHUNKS;
+    const int kvh = rest / CHUNKS;
+    const int col = (rest - kvh * CHUNKS) * COLS + (int)threadIdx.x / TPC;
+    const int4 t = a.splits[sp];
+    const int tok = col / a.G, head = col - tok * a.G;
+    if (tok >= t.y) continue;
+    const int64_t at = ((int64_t)t.z * a.Hkv + kvh) * kPfColumns + col;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float M = kNegInf, den = 0.f;
+    for (int i = 0; i < t.w; i += kMergeBatch) {
+      float2 ml[kMergeBatch];
+      f32x4 x[kMergeBatch];
+#pragma unroll
+      for (int k = 0; k < kMergeBatch; ++k) {
+        const bool live = i + k < t.w;
+        const int64_t p = at + (live ? i + k : i) * stride;
+        ml[k] = a.part_ml[p];
+        x[k] = *reinterpret_cast<const f32x4*>(a.part_acc + p * D + 4 * dl);
+        if (!live) ml[k] = float2{kNegInf, 0.f};
+      }
+      float mc = M;
+#pragma unroll
+      for (int k = 0; k < kMergeBatch; ++k) mc = fmaxf(mc, ml[k].x);
+      const float ms = mc == kNegInf ? 0.f : mc;  // no key seen yet: every weight is 2^-inf = 0
+      const float f = fast_exp2(M - ms);
+      den *= f;
+      acc *= f;
+#pragma unroll
+      for (int k = 0; k < kMergeBatch; ++k) {
+        const float wgt = fast_exp2(ml[k].x - ms);
+        den = __builtin_fmaf(wgt, ml[k].y, den);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(wgt, x[k][e], acc[e]);
+      }
+      M = mc;
+    }
+    const float inv = den > 0.f ? 1.f / den : 0.f;
+    const int64_t o = ((int64_t)(t.x + tok) * a.Hq + kvh * a.G + head) * D + 4 * dl;
+    if (a.out_bf16)
+      *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(a.out) + o) =
+          u32x2{pk_bf16(acc[0] * inv, acc[1] * inv), pk_bf16(acc[2] * inv, acc[3] * inv)};
+    else
+      *reinterpret_cast<f32x4*>(static_cast<float*>(a.out) + o) = acc * inv;
+  }
+}
+
 template <KvType KV, int D>
-void* prefill_fn(bool img) {
+void* prefill_fn(bool img, bool split) {
+  if (split)
+    return img ? reinterpret_cast<void*>(&prefill_split_kernel<KV, D, true>)
+               : reinterpret_cast<void*>(&prefill_split_kernel<KV, D, false>);
   return img ? reinterpret_cast<void*>(&prefill_kernel<KV, D, true>)
              : reinterpret_cast<void*>(&prefill_kernel<KV, D, false>);
 }
 
 template <KvType KV>
-void* prefill_for_d(int D, bool img) {
-  return D == 64 ? prefill_fn<KV, 64>(img) : prefill_fn<KV, 128>(img);
+void* prefill_for_d(int D, bool img, bool split) {
+  return D == 64 ? prefill_fn<KV, 64>(img, split) : prefill_fn<KV, 128>(img, split);
 }
 
 template <KvType KV>
@@ -1045,6 +1320,15 @@ hipError_t launch_prefill(const PrefillArgs& a, KvType kv, hipStream_t s) {
   void* params[] = {&args};
   const bool img = a.v_img != nullptr;
   hipError_t e;
+  void* fn = kv == KvType::FP8 ? prefill_for_d<KvType::FP8>(a.D, img, a.slots > 0)
+                                   : prefill_for_d<KvType::BF16>(a.D, img, a.slots > 0);
+  // the persistent grid: one workgroup per CU (two waves per SIMD fill its
+  // registers), a multiple of 8 (the queues' start assumes it), no more than
+  // the units need
+  int64_t wgs = a.cus;
+  const int64_t need = ((int64_t)(a.items_max + a.slots) * a.Hkv + 7) / 8 * 8;
+  wgs = wgs < need ? wgs : need;
+  args.wgs = (int32_t)(wgs / 8 * 8 > 8 ? wgs / 8 * 8 : 8);
   if (img) {  // the plan and the image in one launch
     const int64_t cps = (a.max_blocks + kImgBlocks - 1) / kImgBlocks;
     void* prep = kv == KvType::FP8 ? prep_for_d<KvType::FP8>(a.D) : prep_for_d<KvType::BF16>(a.D);
@@ -1053,24 +1337,11 @@ hipError_t launch_prefill(const PrefillArgs& a, KvType kv, hipStream_t s) {
     e = hipLaunchKernel(reinterpret_cast<void*>(&prefill_plan_kernel), dim3(1), dim3(kPlanThreads), params, 0, s);
   }
   if (e != hipSuccess) return e;
-  void* fn = kv == KvType::FP8 ? prefill_for_d<KvType::FP8>(a.D, img) : prefill_for_d<KvType::BF16>(a.D, img);
-  // the persistent grid: resident workgroups per CU times the CUs, a multiple
-  // of 8 (the queues' start assumes it), no more than the units need
-  static std::atomic<int> per_cu_memo[8];  // per kernel, queried once
-  const int slot = (kv == KvType::FP8 ? 4 : 0) + (a.D == 128 ? 2 : 0) + (img ? 1 : 0);
-  int per_cu = per_cu_memo[slot].load(std::memory_order_relaxed);
-  if (per_cu == 0) {
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kPfThreads, 0);
-    if (e != hipSuccess) return e;
-    per_cu = per_cu > 0 ? per_cu : 1;
-    per_cu_memo[slot].store(per_cu, std::memory_order_relaxed);
-  }
-  const int64_t units = (int64_t)a.items_max * a.Hkv;
-  int64_t wgs = (int64_t)per_cu * a.cus;
-  const int64_t need = (units + 7) / 8 * 8;
-  wgs = wgs < need ? wgs : need;
-  wgs = wgs / 8 * 8 > 8 ? wgs / 8 * 8 : 8;
-  return hipLaunchKernel(fn, dim3((unsigned)wgs), dim3(kPfThreads), params, 0, s);
+  if ((e = hipLaunchKernel(fn, dim3((unsigned)args.wgs), dim3(kPfThreads), params, 0, s)) != hipSuccess) return e;
+  if (a.slots <= 0) return hipSuccess;
+  void* merge = a.D == 64 ? reinterpret_cast<void*>(&prefill_merge_kernel<64>)
+                          : reinterpret_cast<void*>(&prefill_merge_kernel<128>);
+  return hipLaunchKernel(merge, dim3((unsigned)(4 * a.cus)), dim3(kMergeThreads), params, 0, s);
 }
 
 }  // namespace pda
