@@ -375,16 +375,18 @@ typedef struct pda_prefill_problem {
  * the P . V product as fp16 (11 significant bits; bf16 V converts exactly),
  * accumulated in fp32. A live V value beyond +-65504 saturates (status bit 16).
  *
- * Image: each call first converts every cache tile that its sequences read
+ * Image: a call of 8 or more query tiles (of 256 / G tokens) per sequence on
+ * average (PDA_PREFILL_IMAGE_MIN_TILES in the environment, read on every call,
+ * sets another number) first converts every cache tile that its sequences read
  * into the stream's workspace, in the products' operand types (V to fp16, and
  * for an fp8 cache K codes to bf16), indexed like the cache; the attention
  * kernel then copies tiles from that image straight into LDS. The image takes
  * num_blocks * num_kv_heads * 16 * head_dim * 2 bytes (twice that for an fp8
- * cache). When that exceeds the environment variable PDA_PREFILL_IMAGE_MAX_MB
- * (MiB, read on every call; default 8192), when a stream being captured into a
- * HIP graph has too small a workspace for it, or when its allocation fails, the
- * kernel converts each tile in registers instead. Both ways give bit-identical
- * outputs.
+ * cache). With fewer tiles, when the image exceeds the environment variable
+ * PDA_PREFILL_IMAGE_MAX_MB (MiB, read on every call; default 8192), when a
+ * stream being captured into a HIP graph has too small a workspace for it, or
+ * when its allocation fails, the kernel converts each tile in registers instead.
+ * Both ways give bit-identical outputs.
  *
  * Device-checked: lengths are clamped as in decode (status bit 1), block-table
  * entries outside [0, num_blocks) are skipped (bit 2), and offsets that are not

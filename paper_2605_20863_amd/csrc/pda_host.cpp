@@ -586,6 +586,17 @@ int64_t prefill_image_cap() {
   return mb > (INT64_MAX >> 20) ? INT64_MAX : (int64_t)mb << 20;
 }
 
+// Query tiles per sequence (the call's average) from which a prefill writes
+// the image: PDA_PREFILL_IMAGE_MIN_TILES (read on each call; 0 writes it
+// whenever it fits), kPfImageTiles by default.
+int64_t prefill_image_tiles() {
+  const char* v = std::getenv("PDA_PREFILL_IMAGE_MIN_TILES");
+  if (!v || !*v) return pda::kPfImageTiles;
+  char* end = nullptr;
+  const long long n = std::strtoll(v, &end, 10);
+  return end == v || n < 0 || n > INT32_MAX ? pda::kPfImageTiles : (int64_t)n;
+}
+
 int prefill_run(const void* q, const int32_t* q_offsets, const void* k_cache, const void* v_cache,
                 const int32_t* block_table, const int32_t* seq_lens, const float* kv_scales, void* out,
                 float softmax_scale, const pda_prefill_problem* pr, hipStream_t stream) {
@@ -684,7 +695,13 @@ int prefill_run(const void* q, const int32_t* q_offsets, const void* k_cache, co
   const int64_t img_half = pr->num_blocks * pr->num_kv_heads * (int64_t)pda::kBlockSize * pr->head_dim * 2;
   const int64_t img_bytes = kd == PDA_DTYPE_FP8_E4M3 ? 2 * img_half : img_half;
   const bool cap = capturing(stream);
-  bool use_img = img_bytes <= prefill_image_cap();
+  // The image pays where several tiles read what it converts once. Measured
+  // (image against converting in the kernel, us per call, bf16 / fp8 caches, 32
+  // query and 8 KV heads): one tile per sequence, 64 sequences of 2k tokens 355
+  // against 222 / 417 against 218; 8 tiles per sequence, one of 16k tokens 211
+  // against 205 / 216 against 211; 16 tiles 344 against 354 / 354 against 369.
+  bool use_img = img_bytes <= prefill_image_cap() &&
+                 pr->num_tokens / TQ >= prefill_image_tiles() * pr->num_seqs;
   int64_t base_bytes = slots ? split_bytes : plain_bytes;
   if (cap && ws->bytes < base_bytes) slots = 0, base_bytes = plain_bytes;
   if (use_img && cap && ws->bytes < align_up(base_bytes) + img_bytes) use_img = false;

@@ -123,6 +123,7 @@ constexpr int kPfBuckets = 2048; // length classes of the plan's counting sort
 constexpr int kPfSplitUnits = 8;
 constexpr int kPfSplitTiles = 2048;
 constexpr int kPfSplitSeqs = 1024;
+constexpr int kPfImageTiles = 8;   // query tiles per sequence from which the image is written
 constexpr int kPfSplitPairs = 16;  // fewest 32-key pairs a split makes per item
 
 struct PrefillArgs {

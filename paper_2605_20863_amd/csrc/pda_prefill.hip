@@ -41,8 +41,8 @@
 //   while a step computes two pairs, the next two pairs' tiles travel to the
 //   other two buffers. On the image path they go straight from memory to LDS
 //   (global_load_lds, two 16-byte pieces per lane and pair, no registers and
-//   no conversion instructions); on the staging path (an image larger than the
-//   host allows) each thread loads its pieces into registers, converts them and
+//   no conversion instructions); on the staging path (few tiles to share what
+//   an image converts, or an image larger than the host allows) each thread loads its pieces into registers, converts them and
 //   writes them to LDS between the step's two pairs.
 // * Key order: lane group c (lanes 16c .. 16c + 15) holds keys 8c .. 8c + 7 of
 //   a pair in its score and P^T registers, 8 consecutive tokens of one block,
