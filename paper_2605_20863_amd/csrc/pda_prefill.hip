@@ -22,7 +22,7 @@
 //   plan cuts a tile's keys into several items; each writes its unnormalised
 //   output and softmax state, and a merge kernel combines them. Measured, 512
 //   tokens over 16,182 cached ones, 28 / 4 heads, bf16: 462 us per call whole,
-//   164 us split (prep 18, attention 130, merge 8); 64-token turns of 16
+//   155 us split (prep 18, attention 120, merge 8); 64-token turns of 16
 //   sequences over an fp8 cache, 32 / 8 heads: 234 against 178.
 // * Attention kernel: a persistent grid, one workgroup (8 waves, 2 per SIMD)
 //   per CU, that takes (item, KV head) units from queues, so a CU goes from one
@@ -1132,7 +1132,10 @@ __device__ __forceinline__ void pf_body(const PrefillArgs& a) {
       s_next[k & 1] = code;
     }
     __syncthreads();
-    for (int j2 = p0; j2 < npairs; j2 += 2) {
+    // i: pairs since the item's first. The LDS buffers go by it, not by p0 + i:
+    // with p0's low bits unknown the buffer addresses cost 4-8% per pair.
+    for (int i = 0; i < npairs - p0; i += 2) {
+      const int j2 = p0 + i;
       // blocks 2ja .. 2jb + 1 lie in one chunk of 64 (2ja is a multiple of 4, or jb = ja)
       const int ja = j2 + 2 < npairs ? j2 + 2 : npairs - 1, jb = j2 + 3 < npairs ? j2 + 3 : npairs - 1;
       pf_ids_advance(ids, row, ja >> 5, nblk);
@@ -1140,8 +1143,8 @@ __device__ __forceinline__ void pf_body(const PrefillArgs& a) {
       const PfPair pb = pf_pair<KV, IMG>(a, ids, 2 * jb, nblk, nkeys, kvh, status);
       PfStage<KV, D> sa, sb;
       if constexpr (IMG) {
-        if (j2 + 2 < npairs) pf_dma<KV, D>(kimg, vimg, pa.t0, pa.t1, pl, lds0 + ((j2 + 2) & 3) * C::BUF);
-        if (j2 + 3 < npairs) pf_dma<KV, D>(kimg, vimg, pb.t0, pb.t1, pl, lds0 + ((j2 + 3) & 3) * C::BUF);
+        if (j2 + 2 < npairs) pf_dma<KV, D>(kimg, vimg, pa.t0, pa.t1, pl, lds0 + ((i + 2) & 3) * C::BUF);
+        if (j2 + 3 < npairs) pf_dma<KV, D>(kimg, vimg, pb.t0, pb.t1, pl, lds0 + ((i + 3) & 3) * C::BUF);
       } else {
         pf_load<KV, D>(sa, a, pa.t0, pa.t1);
         pf_load<KV, D>(sb, a, pb.t0, pb.t1);
@@ -1150,10 +1153,10 @@ __device__ __forceinline__ void pf_body(const PrefillArgs& a) {
       if (j2 < wpairs) {
         // pair j2 + 1's K pieces are read during pair j2's P . V (even when
         // this wave skips pair j2 + 1: the buffer is in bounds)
-        const uint8_t* ba = lds + (j2 & 3) * C::BUF;
-        const uint8_t* bb = lds + ((j2 + 1) & 3) * C::BUF;
+        const uint8_t* ba = lds + (i & 3) * C::BUF;
+        const uint8_t* bb = lds + ((i + 1) & 3) * C::BUF;
 #pragma unroll
-        for (int i = 0; i < C::MT; ++i) pf_kread<KV, D>(ba, o, i);
+        for (int m = 0; m < C::MT; ++m) pf_kread<KV, D>(ba, o, m);
         f32x4 s0[kPfNT], s1[kPfNT];
         pf_scores<KV, D, IMG>(o, qb, s0, s1, ba);
         finish(std::true_type{}, std::integral_constant<bool, !IMG>{}, j2, s0, s1, m0, o, ba, bb);
@@ -1161,14 +1164,14 @@ __device__ __forceinline__ void pf_body(const PrefillArgs& a) {
       const PfMeta m1cur = m1;
       if constexpr (!IMG) {
         if (j2 + 2 < npairs)
-          pf_store<KV, D>(sa, pf_vs(pa, 0), pf_vs(pa, 1), pa.live, lds + ((j2 + 2) & 3) * C::BUF, status);
+          pf_store<KV, D>(sa, pf_vs(pa, 0), pf_vs(pa, 1), pa.live, lds + ((i + 2) & 3) * C::BUF, status);
         if (j2 + 3 < npairs)
-          pf_store<KV, D>(sb, pf_vs(pb, 0), pf_vs(pb, 1), pb.live, lds + ((j2 + 3) & 3) * C::BUF, status);
+          pf_store<KV, D>(sb, pf_vs(pb, 0), pf_vs(pb, 1), pb.live, lds + ((i + 3) & 3) * C::BUF, status);
         m0 = pf_meta(pa, a.scale_log2);
         m1 = pf_meta(pb, a.scale_log2);
       }
       if (j2 + 1 < wpairs) {
-        const uint8_t* bb = lds + ((j2 + 1) & 3) * C::BUF;
+        const uint8_t* bb = lds + ((i + 1) & 3) * C::BUF;
         f32x4 s0[kPfNT], s1[kPfNT];
         pf_scores<KV, D, true>(o, qb, s0, s1, bb);
         finish(std::false_type{}, std::false_type{}, j2 + 1, s0, s1, m1cur, o, bb, bb);
