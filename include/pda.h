@@ -131,7 +131,10 @@ typedef struct pda_plan_info {
  * are cut into equal chunks that persistent waves take in turn (each wave its
  * own first chunk, the rest in arrival order); a sequence split between
  * chunks is finished by a log-sum-exp combine kernel on the same stream. The result does not depend
- * on which wave ran which chunk: repeated calls give identical output.
+ * on which wave ran which chunk: repeated calls give identical output. A call
+ * of few sequences and KV heads with bounded lengths (and no work-split option
+ * set) runs as one kernel instead, each sequence and KV head cut into parts
+ * whose last one to finish merges them, in part order.
  *
  * Ownership: the caller owns every buffer; the library keeps no pointer to
  * them after returning. It owns one device workspace per (device, stream),
@@ -145,7 +148,9 @@ typedef struct pda_plan_info {
  * replays. A call that would grow the workspace during capture returns
  * PDA_EINVAL instead of allocating; growth after a capture keeps the old
  * allocation for the graph until pda_release_workspaces(), after which no
- * graph captured before may be replayed. This holds for every call below.
+ * graph captured before may be replayed. A graph works in the workspace of the
+ * stream it was captured on: its replays must not overlap each other, calls on
+ * that stream, or other graphs captured on it. This holds for every call below.
  *
  * Errors: all argument checks run on the host before any HIP call, so invalid
  * arguments return PDA_EINVAL / PDA_EUNSUPPORTED without touching a device.
@@ -189,7 +194,7 @@ int pda_paged_decode_attention(const void* q,
  * from several threads are serialised by an internal lock, as are calls on
  * different devices. The chunk counter starts at zero (the array is
  * zero-initialised at load) and the combine kernel re-zeroes it after every
- * call. Status bits go to the array's status word, which
+ * call; the counts of the one-kernel form are cleared before each. Status bits go to the array's status word, which
  * pda_read_device_status(stream) reads and clears too (after waiting for
  * `stream` only).
  *

@@ -23,6 +23,7 @@
 #include <utility>
 #include <vector>
 
+static_assert(pda::kHdrWords * 4 <= 256, "the header's room in every workspace layout");
 static_assert(pda::kScratchBytes == PDA_NOALLOC_SCRATCH_BYTES, "fixed scratch size differs from the header's");
 
 namespace {
@@ -388,6 +389,39 @@ int query_plan(const pda_problem* problem, const pda_options* options, float sof
   return PDA_OK;
 }
 
+// Parts per unit of the short decode kernel, or 0 for the stream-K kernels.
+// The host knows the units and the bound on the lengths, not the lengths. The
+// line lies where the stream-K kernels, which share the whole batch's blocks
+// evenly, were not yet ahead on lognormal lengths (sigma 0.5, the bound at the
+// longest; us per call, stream-K against short, bf16, 28 / 4 heads): 4 units of
+// 64 tokens 17.1 against 4.2, of 12,000 38.4 / 17.5; 32 units of 1,000 tokens
+// 20.3 / 10.9, of 12,000 54.7 / 47.6; 64 units of 1,000 21.3 / 13.0, of 3,000
+// 32.0 / 26.5, of 12,000 84.5 / 87.2; 128 units of 300 19.5 / 13.1, of 1,000
+// 25.9 / 28.1, of 3,000 47.4 / 71.2. The first bound is on the steps a wave
+// runs one after the other when one sequence has the longest length (12 at 256
+// compute units; half the length for the two-tile body and for f32 caches, whose
+// steps take about twice as long per token), the second on the work in flight,
+// which grows with units and length.
+int short_parts(const pda_problem* pr, const Plan& plan, const Groups& gr, const pda_options* op, int cus,
+                int chunks_max) {
+  // f32 caches and the MFMA body; options that ask for a split mean the stream's
+  if (gr.on || (plan.variant == pda::Variant::Vector && plan.kv != pda::KvType::F32)) return 0;
+  if (op && (op->waves_per_cu || op->min_blocks_per_wave || op->chunks_per_wave || op->min_blocks_per_chunk)) return 0;
+  const int64_t units = (int64_t)pr->num_seqs * pr->num_kv_heads;
+  const bool wide = plan.Q * plan.G > 16, slow = wide || plan.kv == pda::KvType::F32;
+  if (units > pda::kShortUnits || units * plan.len_cap > (slow ? 3 << 16 : 3 << 17) ||
+      units * units * plan.len_cap > 7 << 22)
+    return 0;
+  // one workgroup per compute unit (more gained nothing), a group of steps each at least
+  const int64_t step = plan.kv == pda::KvType::F32 ? 16 : 32;
+  const int64_t groups = (plan.len_cap + step * pda::kShortGroup - 1) / (step * pda::kShortGroup);
+  int64_t parts = cus / units;
+  if (parts > (wide ? pda::kShortParts / 2 : pda::kShortParts)) parts = wide ? pda::kShortParts / 2 : pda::kShortParts;
+  if (parts > groups) parts = groups;
+  if (parts < 1) parts = 1;
+  return units * parts <= units + chunks_max ? (int)parts : 0;  // the layout's partial slots
+}
+
 // fixed_scratch: take the workspace from the device's fixed scratch array
 // (pda_paged_decode_attention_noalloc) instead of the stream's allocation.
 int run(const void* q, const void* k_cache, const void* v_cache, const int32_t* block_table,
@@ -504,6 +538,9 @@ int run(const void* q, const void* k_cache, const void* v_cache, const int32_t* 
   a.ws_m = reinterpret_cast<float*>(base + lay.m);
   a.ws_l = reinterpret_cast<float*>(base + lay.l);
   a.ws_acc = reinterpret_cast<float*>(base + lay.acc);
+  a.short_parts = short_parts(problem, plan, gr, options, di.cus, chunks_max);
+  // calls that overlap on the fixed scratch race; their counts must not outlive them
+  a.short_clear = fixed_scratch;
   if (gr.on && (e = pda::launch_prefix(a, gr.num_groups, stream)) != hipSuccess)
     return fail_hip(e, "prefix kernel launch");
   if ((e = pda::launch_decode(a, plan.variant, plan.kv, stream)) != hipSuccess)

@@ -39,7 +39,17 @@ constexpr int kHdrNext = 2;   // chunk counter of a dynamic split; zero between 
 constexpr int kHdrItems = 3;  // prefill: work items the plan kernel listed
 constexpr int kHdrSplits = 4; // prefill: tiles whose keys the plan split over several items
 constexpr int kHdrPfQueue = 8;  // prefill: words 8..15, the unit counters of the attention grid's queues
-constexpr int kHdrWords = 16;
+constexpr int kHdrArrived = 16; // short decode: words 16..63, a byte per unit: its parts that have arrived; zero between calls
+constexpr int kHdrWords = 64;
+
+// Short decode (see decode_short_kernel): at most this many (sequence, KV head)
+// units, one byte of the header each, and this many parts per unit, half as
+// many with more than 16 query columns (the last workgroup of a unit reads them
+// all, four at a time).
+constexpr int kShortUnits = 4 * (kHdrWords - kHdrArrived);
+constexpr int kShortParts = 32;
+constexpr int kShortWaves = 4;  // waves per workgroup
+constexpr int kShortGroup = 4;  // consecutive steps of a unit that go to one part, one per wave
 
 // Everything one decode step's kernels need. Plain data; passed by value.
 // The decode kernels keep it in registers; two more int32 fields once made
@@ -88,6 +98,8 @@ struct DecodeArgs {
   float* ws_m;          // [slots, Gp] running max (base 2) per partial
   float* ws_l;          // [slots, Gp] softmax denominator per partial
   float* ws_acc;        // [slots, Gp, D] unnormalised output per partial
+  int32_t short_parts;  // > 0: the short decode kernel, with at most this many parts per unit
+  int32_t short_clear;  // 1: clear its arrival counts first
 };
 
 // Number of partial-result slots one call can need: one per (unit, chunk)
@@ -118,8 +130,7 @@ constexpr int kPfColumns = 256;  // query (token, head) columns per workgroup
 constexpr int kPfBuckets = 2048; // length classes of the plan's counting sort
 // A call of at most kPfSplitUnits units (tiles x KV heads) per compute unit is
 // planned with its keys split where the tiles alone leave compute units idle;
-// with more units the queues even them out, and the kernel without the split is
-// a few percent faster per pair.
+// with more units the queues even them out.
 constexpr int kPfSplitUnits = 8;
 constexpr int kPfSplitTiles = 2048;
 constexpr int kPfSplitSeqs = 1024;

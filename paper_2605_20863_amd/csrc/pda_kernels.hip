@@ -392,10 +392,8 @@ struct Blk {
   int rem;
 };
 
-__device__ __forceinline__ Blk block_at(const DecodeArgs& a, BlockIds& ids, int j, int L, int kvh,
-                                        int& status) {
+__device__ __forceinline__ Blk block_of(const DecodeArgs& a, int p, int j, int L, int kvh, int& status) {
   Blk r;
-  int p = ids.get(j);
   int rem = L - j * kBlockSize;
   if ((unsigned)p >= (uint64_t)a.num_blocks) {
     status |= kStatusBadBlock;
@@ -407,6 +405,11 @@ __device__ __forceinline__ Blk block_at(const DecodeArgs& a, BlockIds& ids, int 
   r.lim = rem > kBlockSize ? kBlockSize : rem;
   r.tile = (int64_t)p * a.Hkv + kvh;
   return r;
+}
+
+__device__ __forceinline__ Blk block_at(const DecodeArgs& a, BlockIds& ids, int j, int L, int kvh,
+                                        int& status) {
+  return block_of(a, ids.get(j), j, L, kvh, status);
 }
 
 // One segment: blocks [j_lo, j_hi) of an entry under KV head kvh.
@@ -475,22 +478,22 @@ __device__ __forceinline__ bf16x8 k_operand(const u32x4 (&k)[MfmaCfg<KV, D>::NK4
   }
 }
 
+// Loads of one pair: block b0, and b1 where `two` (otherwise b0's tile again,
+// all of it masked).
 template <KvType KV, int D>
-__device__ __forceinline__ void mfma_issue(MfmaPair<KV, D>& bf, const DecodeArgs& a, BlockIds& ids,
-                                           int j0, int j_hi, int L, int kvh, int& status) {
+__device__ __forceinline__ void mfma_load(MfmaPair<KV, D>& bf, const DecodeArgs& a, const Blk& b0, bool two,
+                                          const Blk& b1) {
   using C = MfmaCfg<KV, D>;
   const int l = lane_id();
   const int r = l & 15, c = l >> 4;
   const uint8_t* kc = static_cast<const uint8_t*>(a.k_cache);
   const uint8_t* vc = static_cast<const uint8_t*>(a.v_cache);
   constexpr int64_t TILE = (int64_t)kBlockSize * D * C::ESZ;  // bytes per (block, head) tile
-  const Blk b0 = block_at(a, ids, j0, L, kvh, status);
-  int64_t tile1 = b0.tile;  // a missing second block reads the first's tile, all of it masked
+  int64_t tile1 = b0.tile;
   bf.rem[0] = b0.rem;
   bf.rem[1] = 0;
   bf.ks[1] = bf.vs[1] = 0.f;
-  if (j0 + 1 < j_hi) {
-    const Blk b1 = block_at(a, ids, j0 + 1, L, kvh, status);
+  if (two) {
     tile1 = b1.tile;
     bf.rem[1] = b1.rem;
     if constexpr (KV == KvType::FP8) {
@@ -518,6 +521,16 @@ __device__ __forceinline__ void mfma_issue(MfmaPair<KV, D>& bf, const DecodeArgs
   const uint8_t* vt = vc + vtile * TILE + (r * kBlockSize + 8 * (c & 1)) * C::ESZ;
 #pragma unroll
   for (int m = 0; m < C::MT; ++m) bf.v[m] = ld_stream<VSlice<KV>>(vt + m * 16 * kBlockSize * C::ESZ);
+}
+
+template <KvType KV, int D>
+__device__ __forceinline__ void mfma_issue(MfmaPair<KV, D>& bf, const DecodeArgs& a, BlockIds& ids,
+                                           int j0, int j_hi, int L, int kvh, int& status) {
+  const Blk b0 = block_at(a, ids, j0, L, kvh, status);
+  Blk b1 = b0;
+  const bool two = j0 + 1 < j_hi;
+  if (two) b1 = block_at(a, ids, j0 + 1, L, kvh, status);
+  mfma_load<KV, D>(bf, a, b0, two, b1);
 }
 
 // Running-max slack (log2 units). The accumulators are rescaled only when a
@@ -896,12 +909,10 @@ __device__ __forceinline__ void decode_elems(float (&f)[N], const uint32_t (&w)[
 }
 
 template <KvType KV, int D>
-__device__ __forceinline__ void vec_issue(VecBlock<KV, D>& bk, const DecodeArgs& a, BlockIds& ids, int j,
-                                          int L, int kvh, int& status) {
+__device__ __forceinline__ void vec_load(VecBlock<KV, D>& bk, const DecodeArgs& a, const Blk& blk) {
   using C = VecCfg<KV, D>;
   const int l = lane_id();
   const int r4 = l >> 4, c16 = l & 15;
-  const Blk blk = block_at(a, ids, j, L, kvh, status);
   bk.lim = blk.lim;
   constexpr int64_t TILE = (int64_t)kBlockSize * D * C::ESZ;
   const uint8_t* kt = static_cast<const uint8_t*>(a.k_cache) + blk.tile * TILE;
@@ -919,6 +930,12 @@ __device__ __forceinline__ void vec_issue(VecBlock<KV, D>& bk, const DecodeArgs&
     bk.ks = 1.f;
     bk.vs = 1.f;
   }
+}
+
+template <KvType KV, int D>
+__device__ __forceinline__ void vec_issue(VecBlock<KV, D>& bk, const DecodeArgs& a, BlockIds& ids, int j,
+                                          int L, int kvh, int& status) {
+  vec_load<KV, D>(bk, a, block_at(a, ids, j, L, kvh, status));
 }
 
 template <KvType KV, int D, int GV, bool MASKED>
@@ -1387,6 +1404,363 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(DecodeArgs a) 
   }
 }
 
+// ------------------------------------------------------------- short decode
+
+// Decode of few (sequence, KV head) units in one launch. Such a call is bound
+// by its chain of dependent round trips and by fetching code: the stream-K
+// kernels run 30-100 KB of mostly straight-line code once, plan from every
+// length and need the combine kernel's launch. Here a unit is cut into parts
+// that do not depend on any length, one workgroup of four waves each; the waves
+// merge through LDS, and where a unit has several live parts, the workgroup
+// that arrives last merges them in part order (the result does not depend on
+// who that is). Code is kept small (8 KB for bf16, D = 128, one N-tile): one
+// masked body for every pair, the next pair's loads copied into its place; two
+// buffers with a body each cost 0.3-0.5 us per call, eight instead of four
+// partials per merge step 0.4, integer divisions by runtime values 0.6.
+// Measured, bf16, 28 / 4 heads, us per call in a HIP graph, stream-K -> here: one
+// sequence of 64 tokens 17.1 -> 4.2, 8 of about 1,000 20.3 -> 10.9, 16 of about
+// 1,000 21.3 -> 13.0.
+//
+// Parts cross XCDs, whose L2s are separate: partials are stored and loaded at
+// agent scope (write-through and past the L2), each workgroup waits for its
+// stores before it counts itself as arrived, and no cache is flushed or
+// invalidated (with agent-scope fences 8 sequences of 1,000 took 24-30 us). The
+// count is a byte of the workspace header, zero between calls; the last
+// workgroup takes its unit's count back to zero.
+
+static_assert(kShortGroup == kShortWaves, "a group is a step per wave");
+constexpr int kShortBatch = 4;  // partials a thread of the last workgroup loads at a time
+
+__device__ __forceinline__ void st_agent(float* p, float x, float y) {
+  const uint64_t v = ((uint64_t)__builtin_bit_cast(uint32_t, y) << 32) | __builtin_bit_cast(uint32_t, x);
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ f32x2 ld_agent(const float* p) {
+  const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return f32x2{__builtin_bit_cast(float, (uint32_t)v), __builtin_bit_cast(float, (uint32_t)(v >> 32))};
+}
+
+// col / G for a column below kWideColumns (the quotient is at least 1 / (2 G)
+// away from the next integer, far beyond the reciprocal's error)
+__device__ __forceinline__ int col_member(int col, float inv_g) { return (int)(((float)col + 0.5f) * inv_g); }
+
+// One wave's steps (pairs of blocks, or blocks for f32 caches) of a unit: the
+// unit's steps go to its parts in groups of four, group g to part g %
+// short_parts, and a group's steps to the four waves. Where a wave's steps lie
+// does not depend on the length, so block ids and queries are loaded beside the
+// length, in one round trip.
+struct ShortPart {
+  const int32_t* row;  // the sequence's block ids
+  int b, kvh;
+  int first, stride;   // the wave's steps: first, first + stride, ... below `steps`
+  int L, nb, steps;    // tokens, blocks, steps of the unit (from the length)
+  float inv_g;         // 1 / G
+};
+
+template <KvType KV, int D, int NT>
+struct ShortMfma {
+  static constexpr KvType kKv = KV;
+  static constexpr int kD = D;
+  static constexpr int kCols = 16 * NT;
+  static constexpr int kStepBlocks = 2;
+  static __device__ __forceinline__ void wave(const DecodeArgs& a, const ShortPart& sp, float* acc_lds, float* m_lds,
+                                              float* l_lds, int& status, bool live) {
+    using C = MfmaCfg<KV, D>;
+    const int l = lane_id();
+    const int r = l & 15, c = l >> 4;
+    // ids of the wave's steps 32k .. 32k + 31: lane i holds block i % 2 of step 32k + i / 2
+    auto load_ids = [&](int k) {
+      const int j = 2 * (sp.first + sp.stride * (32 * k + (l >> 1))) + (l & 1);
+      return sp.row[j < a.max_blocks ? j : a.max_blocks - 1];
+    };
+    int ids = load_ids(0);
+    int hide[NT];
+    bf16x8 qb[NT][C::KSTEPS];
+    const uint32_t qflip = a.neg_scale ? 0x80008000u : 0u;  // a negative scale goes into q's sign
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+      const int col = 16 * k + r;
+      const int mem = col_member(col, sp.inv_g), head = col - mem * a.G;
+      const bool on = col < a.Qn * a.G;
+      hide[k] = on ? a.Qn - 1 - mem : 0;
+      const uint16_t* qrow =
+          static_cast<const uint16_t*>(a.q) + (int64_t)(on ? (sp.b * a.Qn + mem) * a.Hq + sp.kvh * a.G + head : 0) * D;
+#pragma unroll
+      for (int j = 0; j < C::KSTEPS; ++j) {
+        u32x4 x = ld<u32x4>(qrow + C::qdim(j, c));
+        if (!on) x = u32x4{0, 0, 0, 0};
+        qb[k][j] = __builtin_bit_cast(bf16x8, x ^ qflip);
+      }
+    }
+    if (!live) return;
+    f32x4 acc[C::MT][NT];
+    float m_run[NT], l_run[NT];
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+      m_run[k] = kNegInf;
+      l_run[k] = 0.f;
+#pragma unroll
+      for (int m = 0; m < C::MT; ++m) acc[m][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    auto issue = [&](MfmaPair<KV, D>& bf, int t, int step) {
+      if ((t & 31) == 0 && t) ids = load_ids(t >> 5);
+      const int j0 = 2 * step;
+      const int i0 = __builtin_amdgcn_readlane(ids, 2 * (t & 31)), i1 = __builtin_amdgcn_readlane(ids, 2 * (t & 31) + 1);
+      const bool two = j0 + 1 < sp.nb;
+      const Blk b0 = block_of(a, i0, j0, sp.L, sp.kvh, status);
+      int st1 = 0;
+      const Blk b1 = block_of(a, i1, j0 + 1, sp.L, sp.kvh, st1);
+      if (two) status |= st1;
+      mfma_load<KV, D>(bf, a, b0, two, b1);
+    };
+    MfmaPair<KV, D> b0, b1;
+    if (sp.first < sp.steps) issue(b0, 0, sp.first);
+    b1 = b0;
+#pragma unroll 1
+    for (int t = 0, step = sp.first; step < sp.steps; ++t, step += sp.stride) {
+      if (step + sp.stride < sp.steps) issue(b1, t + 1, step + sp.stride);
+      mfma_compute<KV, D, true, NT>(b0, qb, a.mfma_scale_log2, acc, m_run, l_run, hide);
+      b0 = b1;
+    }
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+      float lt = l_run[k];  // lanes c = 0..3 hold disjoint tokens of column r
+      lt += __shfl_xor(lt, 16, 64);
+      lt += __shfl_xor(lt, 32, 64);
+      const int col = 16 * k + r;
+#pragma unroll
+      for (int m = 0; m < C::MT; ++m) *reinterpret_cast<f32x4*>(acc_lds + col * (D + 4) + 16 * m + 4 * c) = acc[m][k];
+      if (c == 0) {
+        m_lds[col] = m_run[k];
+        l_lds[col] = lt;
+      }
+    }
+  }
+};
+
+template <KvType KV, int D, int GV>
+struct ShortVec {
+  static constexpr KvType kKv = KV;
+  static constexpr int kD = D;
+  static constexpr int kCols = 16;  // of them G in use
+  static constexpr int kStepBlocks = 1;
+  static __device__ __forceinline__ void wave(const DecodeArgs& a, const ShortPart& sp, float* acc_lds, float* m_lds,
+                                              float* l_lds, int& status, bool live) {
+    using C = VecCfg<KV, D>;
+    const int l = lane_id();
+    const int r4 = l >> 4, c16 = l & 15;
+    auto load_ids = [&](int k) {  // lane i holds the block of the wave's step 64k + i
+      const int j = sp.first + sp.stride * (64 * k + l);
+      return sp.row[j < a.max_blocks ? j : a.max_blocks - 1];
+    };
+    int ids = load_ids(0);
+    float qf[GV][C::ED], acc[GV][C::ED], m_run[GV], l_run[GV];
+#pragma unroll
+    for (int h = 0; h < GV; ++h) {
+      const float* q = static_cast<const float*>(a.q) +
+                       ((int64_t)sp.b * a.Hq + sp.kvh * a.G + (h < a.G ? h : 0)) * D + c16 * C::ED;
+      m_run[h] = kNegInf;
+      l_run[h] = 0.f;
+#pragma unroll
+      for (int e = 0; e < C::ED; ++e) {
+        qf[h][e] = q[e];
+        acc[h][e] = 0.f;
+      }
+    }
+    if (!live) return;
+    auto issue = [&](VecBlock<KV, D>& bk, int t, int step) {
+      if ((t & 63) == 0 && t) ids = load_ids(t >> 6);
+      vec_load<KV, D>(bk, a, block_of(a, __builtin_amdgcn_readlane(ids, t & 63), step, sp.L, sp.kvh, status));
+    };
+    VecBlock<KV, D> b0, b1;
+    if (sp.first < sp.steps) issue(b0, 0, sp.first);
+    b1 = b0;
+#pragma unroll 1
+    for (int t = 0, step = sp.first; step < sp.steps; ++t, step += sp.stride) {
+      if (step + sp.stride < sp.steps) issue(b1, t + 1, step + sp.stride);
+      vec_compute<KV, D, GV, true>(b0, qf, a.scale_log2, acc, m_run, l_run);
+      b0 = b1;
+    }
+    // each 16-lane row holds its own tokens: total over the four rows
+#pragma unroll
+    for (int h = 0; h < GV; ++h) {
+      l_run[h] += __shfl_xor(l_run[h], 16, 64);
+      l_run[h] += __shfl_xor(l_run[h], 32, 64);
+#pragma unroll
+      for (int e = 0; e < C::ED; ++e) {
+        acc[h][e] += __shfl_xor(acc[h][e], 16, 64);
+        acc[h][e] += __shfl_xor(acc[h][e], 32, 64);
+      }
+      if (r4 == 0) {
+#pragma unroll
+        for (int e = 0; e < C::ED; ++e) acc_lds[h * (D + 4) + c16 + 16 * e] = acc[h][e];
+        if (c16 == 0) {
+          m_lds[h] = m_run[h];
+          l_lds[h] = l_run[h];
+        }
+      }
+    }
+  }
+};
+
+// Folds one partial (m, l, x) of a column into the running (M, den, acc).
+template <int DE>
+__device__ __forceinline__ void fold(float m, float l, const float (&x)[DE], float& M, float& den, float (&acc)[DE]) {
+  const float mc = fmaxf(M, m);
+  const float ms = mc == kNegInf ? 0.f : mc;  // nothing seen yet: both weights are 2^-inf = 0
+  const float f = fast_exp2(M - ms), g = fast_exp2(m - ms);
+  den = den * f + g * l;
+#pragma unroll
+  for (int e = 0; e < DE; ++e) acc[e] = acc[e] * f + g * x[e];
+  M = mc;
+}
+
+template <class W>
+__device__ __forceinline__ void short_body(const DecodeArgs& a) {
+  constexpr int D = W::kD, DE = D / 16, NT = W::kCols / 16;
+  __shared__ __attribute__((aligned(16))) float acc_lds[kShortWaves][W::kCols * (D + 4)];
+  __shared__ float m_lds[kShortWaves][W::kCols], l_lds[kShortWaves][W::kCols];
+  __shared__ int last_lds;
+  const int tid = (int)threadIdx.x;
+  const int wave = uni(tid >> 6);
+  const int kvh = (int)blockIdx.x, b = (int)blockIdx.y, part = (int)blockIdx.z;
+  const int u = b * a.Hkv + kvh;
+  const float inv_g = __builtin_amdgcn_rcpf((float)a.G);
+  const int raw = a.seq_lens[b];
+  ShortPart sp;
+  sp.row = a.block_table + (int64_t)b * a.max_blocks;
+  sp.b = b;
+  sp.kvh = kvh;
+  sp.inv_g = inv_g;
+  sp.first = part * kShortGroup + wave;
+  sp.stride = a.short_parts * kShortGroup;
+  sp.L = clamp_len(a, raw);
+  sp.nb = (sp.L + kBlockSize - 1) / kBlockSize;
+  sp.steps = (sp.nb + W::kStepBlocks - 1) / W::kStepBlocks;
+  int status = sp.L != raw ? kStatusLenClamped : 0;
+  const int groups = (sp.steps + kShortGroup - 1) / kShortGroup;
+  const int parts = groups < 1 ? 1 : groups < a.short_parts ? groups : a.short_parts;
+  W::wave(a, sp, acc_lds[wave], m_lds[wave], l_lds[wave], status, part < parts);
+  if (part >= parts) return;
+  if (status) atomicOr(a.hdr + kHdrStatus, status);  // error paths only
+  __syncthreads();
+
+  // thread t owns column 16n + t / 16 and dims [ (t % 16) * D/16, +D/16 )
+  const int d0 = (tid & 15) * DE;
+  const int ncols = a.Qn * a.G;
+  float acc[NT][DE], M[NT], den[NT];
+#pragma unroll
+  for (int n = 0; n < NT; ++n) {
+    const int col = 16 * n + (tid >> 4);
+    M[n] = kNegInf;
+    den[n] = 0.f;
+#pragma unroll
+    for (int e = 0; e < DE; ++e) acc[n][e] = 0.f;
+    if (col < ncols) {
+#pragma unroll
+      for (int w = 0; w < kShortWaves; ++w) {
+        float x[DE];
+#pragma unroll
+        for (int e = 0; e < DE; e += 4) {
+          const f32x4 v = *reinterpret_cast<const f32x4*>(&acc_lds[w][col * (D + 4) + d0 + e]);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) x[e + i] = v[i];
+        }
+        fold<DE>(m_lds[w][col], l_lds[w][col], x, M[n], den[n], acc[n]);
+      }
+    }
+  }
+  if (parts > 1) {
+    const int64_t slot0 = (int64_t)u * a.short_parts;
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const int col = 16 * n + (tid >> 4);
+      if (col >= ncols) continue;
+      const int64_t at = (slot0 + part) * a.Gp + col;
+#pragma unroll
+      for (int e = 0; e < DE; e += 2) st_agent(a.ws_acc + at * D + d0 + e, acc[n][e], acc[n][e + 1]);
+      if ((tid & 15) == 0) {
+        __hip_atomic_store(a.ws_m + at, M[n], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(a.ws_l + at, den[n], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores have reached memory
+    __syncthreads();
+    if (tid == 0) {
+      int32_t* word = a.hdr + kHdrArrived + (u >> 2);
+      const int shift = 8 * (u & 3);
+      const int before = __hip_atomic_fetch_add(word, 1 << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const bool last = ((before >> shift) & 0xFF) == parts - 1;
+      if (last) __hip_atomic_fetch_sub(word, parts << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      last_lds = last;
+    }
+    __syncthreads();
+    if (!last_lds) return;
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+      const int col = 16 * n + (tid >> 4);
+      M[n] = kNegInf;
+      den[n] = 0.f;
+#pragma unroll
+      for (int e = 0; e < DE; ++e) acc[n][e] = 0.f;
+      if (col >= ncols) continue;
+      #pragma unroll 1
+      for (int p0 = 0; p0 < parts; p0 += kShortBatch) {
+        float m[kShortBatch], l[kShortBatch], x[kShortBatch][DE];
+#pragma unroll
+        for (int i = 0; i < kShortBatch; ++i) {
+          const bool live = p0 + i < parts;
+          const int64_t at = (slot0 + (live ? p0 + i : p0)) * a.Gp + col;
+          m[i] = __hip_atomic_load(a.ws_m + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          l[i] = __hip_atomic_load(a.ws_l + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+          for (int e = 0; e < DE; e += 2) {
+            const f32x2 v = ld_agent(a.ws_acc + at * D + d0 + e);
+            x[i][e] = v.x;
+            x[i][e + 1] = v.y;
+          }
+          if (!live) m[i] = kNegInf;
+        }
+#pragma unroll
+        for (int i = 0; i < kShortBatch; ++i) fold<DE>(m[i], l[i], x[i], M[n], den[n], acc[n]);
+      }
+    }
+  }
+#pragma unroll
+  for (int n = 0; n < NT; ++n) {
+    const int col = 16 * n + (tid >> 4);
+    if (col >= ncols) continue;
+    const float inv = den[n] > 0.f ? 1.f / den[n] : 0.f;  // an empty sequence writes zeros
+    const int mem = col_member(col, inv_g), head = col - mem * a.G;
+    const int64_t o = (int64_t)((b * a.Qn + mem) * a.Hq + kvh * a.G + head) * D + d0;  // rows < 2^31: host bound
+    if (a.out_bf16) {
+      typedef __bf16 bf16xE __attribute__((ext_vector_type(DE)));
+      bf16xE x;
+#pragma unroll
+      for (int e = 0; e < DE; ++e) x[e] = (__bf16)(acc[n][e] * inv);
+      *reinterpret_cast<bf16xE*>(static_cast<uint16_t*>(a.out) + o) = x;
+    } else {
+      f32x4* out = reinterpret_cast<f32x4*>(static_cast<float*>(a.out) + o);
+#pragma unroll
+      for (int e = 0; e < DE; e += 4)
+        out[e / 4] = f32x4{acc[n][e] * inv, acc[n][e + 1] * inv, acc[n][e + 2] * inv, acc[n][e + 3] * inv};
+    }
+  }
+}
+
+__global__ __launch_bounds__(64) void short_clear_kernel(DecodeArgs a) {
+  const int i = kHdrArrived + (int)threadIdx.x;
+  if (i < kHdrWords) a.hdr[i] = 0;
+}
+
+template <class W>
+__global__ __launch_bounds__(64 * kShortWaves) void decode_short_kernel(
+    DecodeArgs a, const void* __restrict__ q, const void* __restrict__ kc, const void* __restrict__ vc,
+    const int32_t* __restrict__ bt, const int32_t* __restrict__ lens, const float* __restrict__ scales) {
+  short_body<W>(with_inputs(a, q, kc, vc, bt, lens, scales));
+}
+
 // ------------------------------------------------------------- shared prefix
 
 // Shared-prefix mode, before the decode kernel: the number of leading blocks
@@ -1491,10 +1865,31 @@ void* pick(Variant v, KvType kv, int D, int G, bool wide) {
   return pick_d<Variant::Vector, KvType::FP8>(D, G, false);
 }
 
+template <KvType KV, int D>
+void* short_mfma(bool wide) {
+  return wide ? reinterpret_cast<void*>(&decode_short_kernel<ShortMfma<KV, D, 2>>)
+              : reinterpret_cast<void*>(&decode_short_kernel<ShortMfma<KV, D, 1>>);
+}
+
+template <int D>
+void* short_f32(int G) {
+  if (G <= 1) return reinterpret_cast<void*>(&decode_short_kernel<ShortVec<KvType::F32, D, 1>>);
+  if (G <= 2) return reinterpret_cast<void*>(&decode_short_kernel<ShortVec<KvType::F32, D, 2>>);
+  if (G <= 4) return reinterpret_cast<void*>(&decode_short_kernel<ShortVec<KvType::F32, D, 4>>);
+  return reinterpret_cast<void*>(&decode_short_kernel<ShortVec<KvType::F32, D, 8>>);
+}
+
+void* pick_short(KvType kv, int D, int G, bool wide) {
+  if (kv == KvType::F32) return D == 64 ? short_f32<64>(G) : short_f32<128>(G);
+  if (kv == KvType::BF16) return D == 64 ? short_mfma<KvType::BF16, 64>(wide) : short_mfma<KvType::BF16, 128>(wide);
+  return D == 64 ? short_mfma<KvType::FP8, 64>(wide) : short_mfma<KvType::FP8, 128>(wide);
+}
+
 }  // namespace
 
 hipError_t launch_decode(const DecodeArgs& a, Variant v, KvType kv, hipStream_t s) {
-  void* fn = pick(v, kv, a.D, a.G, a.Gp > 16);
+  const bool parts = a.short_parts > 0;
+  void* fn = parts ? pick_short(kv, a.D, a.G, a.Gp > 16) : pick(v, kv, a.D, a.G, a.Gp > 16);
   if (!fn) return hipErrorInvalidValue;
   DecodeArgs args = a;
   const void* q = a.q;
@@ -1504,11 +1899,19 @@ hipError_t launch_decode(const DecodeArgs& a, Variant v, KvType kv, hipStream_t 
   const int32_t* lens = a.seq_lens;
   const float* scales = a.kv_scales;
   void* params[] = {&args, &q, &kc, &vc, &bt, &lens, &scales};
+  if (parts && a.short_clear) {
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<void*>(&short_clear_kernel), dim3(1), dim3(64), params, 0, s);
+    if (e != hipSuccess) return e;
+  }
+  if (parts)
+    return hipLaunchKernel(fn, dim3((unsigned)a.Hkv, (unsigned)a.B, (unsigned)a.short_parts),
+                           dim3(64 * kShortWaves), params, 0, s);
   const int wpg = a.waves_per_group;
   return hipLaunchKernel(fn, dim3(a.waves / wpg), dim3(64 * wpg), params, 0, s);
 }
 
 hipError_t launch_combine(const DecodeArgs& a, hipStream_t s) {
+  if (a.short_parts > 0) return hipSuccess;  // the short kernel merges its own parts
   void* fn;
   if (a.out_bf16)
     fn = a.D == 64 ? reinterpret_cast<void*>(&combine_kernel<true, 64>)
