@@ -160,6 +160,12 @@ struct PrefillArgs {
   int32_t nq;           // unit queues: gcd(Hkv, 8)
   int32_t* hdr;         // workspace header (status, item count, queue counters)
   int4* items;          // [items_max + slots] {sequence, first q row, tokens, first position}
+  // Image of the cache's tiles in the products' operand types, indexed like the
+  // cache (block * Hkv + KV head, 16 * D two-byte elements per tile): V in fp16
+  // (v_img), and for an fp8 cache K in bf16 (k_img). v_img null: the attention
+  // kernel stages the tiles through registers instead.
+  void* k_img;
+  void* v_img;
   // Split plan (slots > 0): every item also has an entry in `parts` {first
   // 32-key pair, end pair, partial slot or -1, 0}. A tile whose keys are split
   // over several items has one slot per item and an entry in `splits` {first q
@@ -172,12 +178,6 @@ struct PrefillArgs {
   int4* splits;         // [slots / 2]
   float2* part_ml;      // [slots, Hkv, kPfColumns] running max (base 2), denominator
   float* part_acc;      // [slots, Hkv, kPfColumns, D]
-  // Image of the cache's tiles in the products' operand types, indexed like the
-  // cache (block * Hkv + KV head, 16 * D two-byte elements per tile): V in fp16
-  // (v_img), and for an fp8 cache K in bf16 (k_img). v_img null: the attention
-  // kernel stages the tiles through registers instead.
-  void* k_img;
-  void* v_img;
 };
 
 hipError_t launch_prefill(const PrefillArgs& a, KvType kv, hipStream_t s);

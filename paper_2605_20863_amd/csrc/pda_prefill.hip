@@ -582,7 +582,7 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PrefillArgs 
 
 // The plan (workgroup 0) and the image (the others) in one launch.
 template <KvType KV, int D>
-__global__ __launch_bounds__(kPlanThreads, 8) void prefill_prep_kernel(PrefillArgs a) {
+__global__ __launch_bounds__(kPlanThreads) void prefill_prep_kernel(PrefillArgs a) {
   if (blockIdx.x == 0) {
     pf_plan(a);
     return;
@@ -984,8 +984,20 @@ __device__ __forceinline__ void pf_pv(PfOps<KV, D>& o, const f16x8 (&ph)[kPfNT],
   }
 }
 
-template <KvType KV, int D, bool IMG, bool SPLIT>
-__device__ __forceinline__ void pf_body(const PrefillArgs& a) {
+// The attention kernel's two instances per cache type, head size and tile
+// source: every item a whole tile, or items that may hold part of a tile's keys.
+// (One kernel template: a shared device function called from two kernels
+// compiled to other code, 2-3% slower for fp8 caches.)
+struct whole_prefill_kernel {
+  static constexpr bool kSplit = false;
+};
+struct split_prefill {
+  static constexpr bool kSplit = true;
+};
+
+template <KvType KV, int D, bool IMG, class Plan>
+__global__ __launch_bounds__(kPfThreads) void prefill_attention(PrefillArgs a) {
+  constexpr bool SPLIT = Plan::kSplit;
   using C = PfCfg<KV, D>;
   __shared__ __attribute__((aligned(16))) uint8_t lds[4 * C::BUF];
   __shared__ int s_next[2];
@@ -1221,16 +1233,6 @@ __device__ __forceinline__ void pf_body(const PrefillArgs& a) {
   if (status) atomicOr(a.hdr + kHdrStatus, status);  // error paths only
 }
 
-template <KvType KV, int D, bool IMG>
-__global__ __launch_bounds__(kPfThreads) void prefill_kernel(PrefillArgs a) {
-  pf_body<KV, D, IMG, false>(a);
-}
-
-template <KvType KV, int D, bool IMG>
-__global__ __launch_bounds__(kPfThreads) void prefill_split_kernel(PrefillArgs a) {
-  pf_body<KV, D, IMG, true>(a);
-}
-
 // Merge of the split tiles' partials: D / 4 threads per query column, 4 dims
 // each, walk the column's partials,
 //     out = sum_i 2^(m_i - M) acc_i / sum_i 2^(m_i - M) l_i,   M = max_i m_i,
@@ -1298,10 +1300,10 @@ __global__ __launch_bounds__(kMergeThreads) void prefill_merge_kernel(PrefillArg
 template <KvType KV, int D>
 void* prefill_fn(bool img, bool split) {
   if (split)
-    return img ? reinterpret_cast<void*>(&prefill_split_kernel<KV, D, true>)
-               : reinterpret_cast<void*>(&prefill_split_kernel<KV, D, false>);
-  return img ? reinterpret_cast<void*>(&prefill_kernel<KV, D, true>)
-             : reinterpret_cast<void*>(&prefill_kernel<KV, D, false>);
+    return img ? reinterpret_cast<void*>(&prefill_attention<KV, D, true, split_prefill>)
+               : reinterpret_cast<void*>(&prefill_attention<KV, D, false, split_prefill>);
+  return img ? reinterpret_cast<void*>(&prefill_attention<KV, D, true, whole_prefill_kernel>)
+             : reinterpret_cast<void*>(&prefill_attention<KV, D, false, whole_prefill_kernel>);
 }
 
 template <KvType KV>

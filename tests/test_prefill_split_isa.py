@@ -8,7 +8,7 @@ from tests.test_prefill_isa import test_no_other_reads_of_m0 as no_other_reads_o
 
 
 def test_split_kernels_m0(prefill_asm):  # noqa: F811
-    asm = "\n".join(re.sub(r"^(_Z\S*)prefill_split_kernel", r"\1split_prefill_kernel", line)
+    asm = "\n".join(re.sub(r"^(_Z\S*)split_prefill", r"\1split_prefill_kernel", line)
                     for line in prefill_asm.splitlines())
     split = {n: ins for n, ins in kernels(asm).items() if "split" in n}
     assert len(split) == 8, sorted(split)
