@@ -236,48 +236,93 @@ def query_plan(problem: Problem, options: Options | None = None, softmax_scale: 
 
 
 # ------------------------------------------------------------------ torch front end
+#
+# A small call's kernels take 3-5 us, so what is done per call here counts:
+# checks are one pass over the tensors (the error to raise is worked out only
+# when one fails), the device is switched only when it is not the current one,
+# and default options are passed as NULL. Nothing is remembered between calls.
 
 def _torch():
-    import torch  # noqa: WPS433 - imported lazily: the ABI tests run without it
-    return torch
+    if _torch_rt is None:
+        raise ImportError("the torch front end needs torch")
+    return _torch_rt
+
+
+if _torch_rt is not None:
+    _DTYPES = {_torch_rt.float32: F32, _torch_rt.bfloat16: BF16, _torch_rt.uint8: FP8_E4M3,
+               _torch_rt.float8_e4m3fn: FP8_E4M3}
+    _INT32, _FLOAT32 = _torch_rt.int32, _torch_rt.float32
+    # the current stream's handle without a Stream object around it
+    _raw_stream = getattr(_torch_rt._C, "_cuda_getCurrentRawStream", None)
 
 
 def _dtype_code(t, what):
-    torch = _torch()
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
-        return BF16
-    if t.dtype in (torch.uint8, torch.float8_e4m3fn):
-        return FP8_E4M3
-    raise TypeError(f"{what}: unsupported dtype {t.dtype}")
+    code = _DTYPES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"{what}: unsupported dtype {t.dtype}")
+    return code
 
 
 def _stream_handle(stream, device):
-    torch = _torch()
     if stream is None:
-        stream = torch.cuda.current_stream(device)
-    return ctypes.c_void_p(stream.cuda_stream)
+        stream = _torch().cuda.current_stream(device)
+    return stream.cuda_stream
+
+
+def _check_tensors(tensors):
+    """Every tensor contiguous on the first one's HIP device (its index is returned)."""
+    first = next(iter(tensors.values()))
+    index = first.get_device()
+    if first.is_cuda:
+        for t in tensors.values():
+            if t.get_device() != index or not t.is_contiguous():
+                break
+        else:
+            return index
+    dev = first.device
+    for name, t in tensors.items():
+        if not t.is_cuda or t.device != dev:
+            raise ValueError(f"{name} must be on {dev}")
+        if not t.is_contiguous():
+            raise ValueError(f"{name} must be contiguous")
+    return index
+
+
+def _launch(fn, index, stream, *args):
+    """fn(*args, stream) with device ``index`` current; raises on an error code."""
+    cuda = _torch_rt.cuda
+    if stream is None and _raw_stream is not None:
+        handle = _raw_stream(index)
+    else:
+        handle = _stream_handle(stream, index)
+    if index == cuda.current_device():
+        rc = fn(*args, handle)
+    else:
+        with cuda.device(index):
+            rc = fn(*args, handle)
+    if rc != OK:
+        _check(rc)
 
 
 def problem_for(q, k_cache, v_cache, block_table, seq_lens, max_seq_len=0, out=None) -> Problem:
     """Problem descriptor from tensor shapes and dtypes (checks they agree).
     q is [num_seqs, num_q_heads, head_dim], or [num_seqs, q_tokens, num_q_heads,
     head_dim] for several query tokens per sequence."""
-    if q.dim() == 4:
-        B, ntok, hq, d = q.shape
-    elif q.dim() == 3:
-        (B, hq, d), ntok = q.shape, 1
+    qs, ks, bts = q.shape, k_cache.shape, block_table.shape
+    if len(qs) == 4:
+        B, ntok, hq, d = qs
+    elif len(qs) == 3:
+        (B, hq, d), ntok = qs, 1
     else:
         raise ValueError("q must be [num_seqs, num_q_heads, head_dim] or [num_seqs, q_tokens, num_q_heads, head_dim]")
-    if k_cache.dim() != 4 or v_cache.dim() != 4:
+    if len(ks) != 4 or v_cache.dim() != 4:
         raise ValueError("k_cache must be [NB, Hkv, 16, D] and v_cache [NB, Hkv, D, 16]")
-    nb, hkv, bs, dk = k_cache.shape
-    if tuple(v_cache.shape) != (nb, hkv, dk, bs):
+    nb, hkv, bs, dk = ks
+    if v_cache.shape != (nb, hkv, dk, bs):
         raise ValueError(f"v_cache shape {tuple(v_cache.shape)} != {(nb, hkv, dk, bs)} (dim-major tiles)")
     if dk != d:
         raise ValueError(f"head_dim mismatch: q {d}, cache {dk}")
-    if block_table.dim() != 2 or block_table.shape[0] != B:
+    if len(bts) != 2 or bts[0] != B:
         raise ValueError("block_table must be [num_seqs, max_blocks_per_seq]")
     if seq_lens.shape != (B,):
         raise ValueError("seq_lens must be [num_seqs]")
@@ -286,7 +331,7 @@ def problem_for(q, k_cache, v_cache, block_table, seq_lens, max_seq_len=0, out=N
         raise TypeError("k_cache and v_cache dtypes differ")
     q_dt = _dtype_code(q, "q")
     out_dt = _dtype_code(out, "out") if out is not None else q_dt
-    return Problem(B, hq, hkv, d, bs, block_table.shape[1], nb, int(max_seq_len), q_dt, kv_dt, out_dt, ntok)
+    return Problem(B, hq, hkv, d, bs, bts[1], nb, int(max_seq_len), q_dt, kv_dt, out_dt, ntok)
 
 
 def paged_decode_attention(q, k_cache, v_cache, block_table, seq_lens, kv_scales, out,
@@ -300,14 +345,11 @@ def paged_decode_attention(q, k_cache, v_cache, block_table, seq_lens, kv_scales
     [NB, Hkv, D, 16], fp8 caches as uint8 or float8_e4m3fn codes plus
     kv_scales [2, NB, Hkv] fp32). ``out`` has q's shape and q's dtype or float32.
     """
-    torch = _torch()
-    prob, opts = _prepare(q, k_cache, v_cache, block_table, seq_lens, kv_scales, out, max_seq_len,
-                          variant, waves_per_cu, min_blocks_per_wave, chunks_per_wave, min_blocks_per_chunk)
-    with torch.cuda.device(q.device):
-        rc = raw_call(q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), block_table.data_ptr(),
-                      seq_lens.data_ptr(), kv_scales.data_ptr() if kv_scales is not None else None,
-                      out.data_ptr(), float(softmax_scale), prob, opts, _stream_handle(stream, q.device))
-    _check(rc)
+    prob, opts, index = _prepare(q, k_cache, v_cache, block_table, seq_lens, kv_scales, out, max_seq_len,
+                                 variant, waves_per_cu, min_blocks_per_wave, chunks_per_wave, min_blocks_per_chunk)
+    _launch(_lib.pda_paged_decode_attention, index, stream, q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(),
+            block_table.data_ptr(), seq_lens.data_ptr(), kv_scales.data_ptr() if kv_scales is not None else None,
+            out.data_ptr(), float(softmax_scale), prob, opts)
     return out
 
 
@@ -318,14 +360,11 @@ def paged_decode_attention_noalloc(q, k_cache, v_cache, block_table, seq_lens, k
     """paged_decode_attention through the entry point that allocates nothing:
     its workspace is the library's fixed per-device scratch array
     (NOALLOC_SCRATCH_BYTES), shared by every call on the device."""
-    torch = _torch()
-    prob, opts = _prepare(q, k_cache, v_cache, block_table, seq_lens, kv_scales, out, max_seq_len,
-                          variant, waves_per_cu, min_blocks_per_wave, chunks_per_wave, min_blocks_per_chunk)
-    with torch.cuda.device(q.device):
-        rc = raw_call_noalloc(q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), block_table.data_ptr(),
-                              seq_lens.data_ptr(), kv_scales.data_ptr() if kv_scales is not None else None,
-                              out.data_ptr(), float(softmax_scale), prob, opts, _stream_handle(stream, q.device))
-    _check(rc)
+    prob, opts, index = _prepare(q, k_cache, v_cache, block_table, seq_lens, kv_scales, out, max_seq_len,
+                                 variant, waves_per_cu, min_blocks_per_wave, chunks_per_wave, min_blocks_per_chunk)
+    _launch(_lib.pda_paged_decode_attention_noalloc, index, stream, q.data_ptr(), k_cache.data_ptr(),
+            v_cache.data_ptr(), block_table.data_ptr(), seq_lens.data_ptr(),
+            kv_scales.data_ptr() if kv_scales is not None else None, out.data_ptr(), float(softmax_scale), prob, opts)
     return out
 
 
@@ -337,88 +376,75 @@ def paged_decode_attention_shared_prefix(q, k_cache, v_cache, block_table, seq_l
     block tables share leading blocks; ``shared_blocks`` is an int32 device
     tensor [num_seqs / group_size] bounding each group's shared blocks (the
     library checks the bound against the block tables)."""
-    torch = _torch()
-    prob, opts = _prepare(q, k_cache, v_cache, block_table, seq_lens, kv_scales, out, max_seq_len,
-                          variant, waves_per_cu, min_blocks_per_wave, chunks_per_wave, min_blocks_per_chunk)
-    if shared_blocks.device != q.device or not shared_blocks.is_contiguous() or shared_blocks.dtype != torch.int32:
+    prob, opts, index = _prepare(q, k_cache, v_cache, block_table, seq_lens, kv_scales, out, max_seq_len,
+                                 variant, waves_per_cu, min_blocks_per_wave, chunks_per_wave, min_blocks_per_chunk)
+    if shared_blocks.device != q.device or not shared_blocks.is_contiguous() or shared_blocks.dtype != _INT32:
         raise ValueError(f"shared_blocks must be a contiguous int32 tensor on {q.device}")
     if group_size < 1 or q.shape[0] % group_size or shared_blocks.numel() != q.shape[0] // group_size:
         raise ValueError("shared_blocks must have num_seqs / group_size entries")
-    with torch.cuda.device(q.device):
-        rc = raw_call_shared_prefix(q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(), block_table.data_ptr(),
-                                    seq_lens.data_ptr(), kv_scales.data_ptr() if kv_scales is not None else None,
-                                    out.data_ptr(), float(softmax_scale), group_size, shared_blocks.data_ptr(),
-                                    prob, opts, _stream_handle(stream, q.device))
-    _check(rc)
+    _launch(_lib.pda_paged_decode_attention_shared_prefix, index, stream, q.data_ptr(), k_cache.data_ptr(),
+            v_cache.data_ptr(), block_table.data_ptr(), seq_lens.data_ptr(),
+            kv_scales.data_ptr() if kv_scales is not None else None, out.data_ptr(), float(softmax_scale),
+            int(group_size), shared_blocks.data_ptr(), prob, opts)
     return out
 
 
 def _prepare(q, k_cache, v_cache, block_table, seq_lens, kv_scales, out, max_seq_len, variant, waves_per_cu,
              min_blocks_per_wave, chunks_per_wave, min_blocks_per_chunk):
-    torch = _torch()
+    """(problem, options or None for the defaults, device index) of a decode call, checked."""
     tensors = {"q": q, "k_cache": k_cache, "v_cache": v_cache, "block_table": block_table,
                "seq_lens": seq_lens, "out": out}
     if kv_scales is not None:
         tensors["kv_scales"] = kv_scales
-    dev = q.device
-    for name, t in tensors.items():
-        if not t.is_cuda or t.device != dev:
-            raise ValueError(f"{name} must be on {dev}")
-        if not t.is_contiguous():
-            raise ValueError(f"{name} must be contiguous")
-    if block_table.dtype != torch.int32 or seq_lens.dtype != torch.int32:
+    index = _check_tensors(tensors)
+    if block_table.dtype != _INT32 or seq_lens.dtype != _INT32:
         raise TypeError("block_table and seq_lens must be int32")
-    if kv_scales is not None and kv_scales.dtype != torch.float32:
+    if kv_scales is not None and kv_scales.dtype != _FLOAT32:
         raise TypeError("kv_scales must be float32")
-    if out.shape != q.shape or out.dtype not in (q.dtype, torch.float32):
+    if out.shape != q.shape or (out.dtype != q.dtype and out.dtype != _FLOAT32):
         raise ValueError("out must have q's shape, and q's dtype or float32")
     prob = problem_for(q, k_cache, v_cache, block_table, seq_lens, max_seq_len, out)
-    if kv_scales is not None and tuple(kv_scales.shape) != (2, prob.num_blocks, prob.num_kv_heads):
+    if kv_scales is not None and kv_scales.shape != (2, prob.num_blocks, prob.num_kv_heads):
         raise ValueError("kv_scales must be [2, num_blocks, num_kv_heads]")
-    opts = make_options(variant, waves_per_cu, min_blocks_per_wave, chunks_per_wave, min_blocks_per_chunk)
-    return prob, opts
+    if variant == "auto" and not (waves_per_cu or min_blocks_per_wave or chunks_per_wave or min_blocks_per_chunk):
+        return prob, None, index
+    return prob, make_options(variant, waves_per_cu, min_blocks_per_wave, chunks_per_wave,
+                              min_blocks_per_chunk), index
 
 
 def paged_kv_append(k_new, v_new, k_cache, v_cache, kv_scales, block_table, positions, stream=None):
     """Enqueue the write of one decode step's new keys / values ([B, Hkv, D],
     float32 or bfloat16) into the paged cache at ``positions`` (int32 [B]);
     layouts as for paged_decode_attention. fp8 caches update ``kv_scales``."""
-    torch = _torch()
     # Shapes first: the kernel reads block_table[b, :] for every b < B, so a
     # table with fewer rows (or a flat one) would be read past its end.
-    if k_new.dim() != 3 or v_new.shape != k_new.shape or v_new.dtype != k_new.dtype:
+    ns, ks, bts = k_new.shape, k_cache.shape, block_table.shape
+    if len(ns) != 3 or v_new.shape != ns or v_new.dtype != k_new.dtype:
         raise ValueError("k_new and v_new must both be [B, Hkv, D] with one dtype")
-    B, hkv, d = k_new.shape
-    if k_cache.dim() != 4 or v_cache.dim() != 4:
+    B, hkv, d = ns
+    if len(ks) != 4 or v_cache.dim() != 4:
         raise ValueError("k_cache must be [NB, Hkv, 16, D] and v_cache [NB, Hkv, D, 16]")
-    nb, hkv2, bs, d2 = k_cache.shape
-    if (hkv2, d2) != (hkv, d) or tuple(v_cache.shape) != (nb, hkv, d, bs) or tuple(positions.shape) != (B,):
+    nb, hkv2, bs, d2 = ks
+    if hkv2 != hkv or d2 != d or v_cache.shape != (nb, hkv, d, bs) or positions.shape != (B,):
         raise ValueError("shapes: k_cache [NB, Hkv, 16, D], v_cache [NB, Hkv, D, 16], positions [B]")
-    if block_table.dim() != 2 or block_table.shape[0] != B:
+    if len(bts) != 2 or bts[0] != B:
         raise ValueError(f"block_table must be [B, max_blocks_per_seq] with B = {B} rows (one per new token), "
-                         f"got {tuple(block_table.shape)}")
+                         f"got {tuple(bts)}")
     tensors = {"k_new": k_new, "v_new": v_new, "k_cache": k_cache, "v_cache": v_cache,
                "block_table": block_table, "positions": positions}
     if kv_scales is not None:
         tensors["kv_scales"] = kv_scales
-    dev = k_new.device
-    for name, t in tensors.items():
-        if not t.is_cuda or t.device != dev:
-            raise ValueError(f"{name} must be on {dev}")
-        if not t.is_contiguous():
-            raise ValueError(f"{name} must be contiguous")
-    if block_table.dtype != torch.int32 or positions.dtype != torch.int32:
+    index = _check_tensors(tensors)
+    if block_table.dtype != _INT32 or positions.dtype != _INT32:
         raise TypeError("block_table and positions must be int32")
     kv_dt = _dtype_code(k_cache, "k_cache")
-    if kv_dt == FP8_E4M3 and (kv_scales is None or tuple(kv_scales.shape) != (2, nb, hkv)
-                              or kv_scales.dtype != torch.float32):
+    if kv_dt == FP8_E4M3 and (kv_scales is None or kv_scales.shape != (2, nb, hkv)
+                              or kv_scales.dtype != _FLOAT32):
         raise ValueError("an fp8 cache needs float32 kv_scales [2, num_blocks, num_kv_heads]")
-    prob = AppendProblem(B, hkv, d, bs, block_table.shape[1], nb, _dtype_code(k_new, "k_new"), kv_dt)
-    with torch.cuda.device(dev):
-        rc = raw_kv_append(k_new.data_ptr(), v_new.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(),
-                           kv_scales.data_ptr() if kv_scales is not None else None, block_table.data_ptr(),
-                           positions.data_ptr(), prob, _stream_handle(stream, dev))
-    _check(rc)
+    prob = AppendProblem(B, hkv, d, bs, bts[1], nb, _dtype_code(k_new, "k_new"), kv_dt)
+    _launch(_lib.pda_paged_kv_append, index, stream, k_new.data_ptr(), v_new.data_ptr(), k_cache.data_ptr(),
+            v_cache.data_ptr(), kv_scales.data_ptr() if kv_scales is not None else None, block_table.data_ptr(),
+            positions.data_ptr(), prob)
 
 
 def paged_prefill_attention(q, q_offsets, k_cache, v_cache, block_table, seq_lens, kv_scales, out,
@@ -435,17 +461,11 @@ def paged_prefill_attention(q, q_offsets, k_cache, v_cache, block_table, seq_len
     unless that exceeds PDA_PREFILL_IMAGE_MAX_MB (default 8192); otherwise the
     kernel converts tiles in registers. The results are the same bit for bit.
     """
-    torch = _torch()
     tensors = {"q": q, "q_offsets": q_offsets, "k_cache": k_cache, "v_cache": v_cache,
                "block_table": block_table, "seq_lens": seq_lens, "out": out}
     if kv_scales is not None:
         tensors["kv_scales"] = kv_scales
-    dev = q.device
-    for name, t in tensors.items():
-        if not t.is_cuda or t.device != dev:
-            raise ValueError(f"{name} must be on {dev}")
-        if not t.is_contiguous():
-            raise ValueError(f"{name} must be contiguous")
+    index = _check_tensors(tensors)
     if q.dim() != 3:
         raise ValueError("q must be [num_tokens, num_q_heads, head_dim]")
     T, hq, d = q.shape
@@ -459,23 +479,20 @@ def paged_prefill_attention(q, q_offsets, k_cache, v_cache, block_table, seq_len
     B = seq_lens.shape[0]
     if q_offsets.shape != (B + 1,):
         raise ValueError("q_offsets must be [num_seqs + 1]")
-    if any(t.dtype != torch.int32 for t in (q_offsets, block_table, seq_lens)):
+    if any(t.dtype != _INT32 for t in (q_offsets, block_table, seq_lens)):
         raise TypeError("q_offsets, block_table and seq_lens must be int32")
     if out.shape != q.shape:
         raise ValueError("out must have q's shape")
     kv_dt = _dtype_code(k_cache, "k_cache")
     if _dtype_code(v_cache, "v_cache") != kv_dt:
         raise TypeError("k_cache and v_cache dtypes differ")
-    if kv_scales is not None and (tuple(kv_scales.shape) != (2, nb, hkv) or kv_scales.dtype != torch.float32):
+    if kv_scales is not None and (tuple(kv_scales.shape) != (2, nb, hkv) or kv_scales.dtype != _FLOAT32):
         raise ValueError("kv_scales must be float32 [2, num_blocks, num_kv_heads]")
     prob = PrefillProblem(B, T, hq, hkv, d, bs, block_table.shape[1], nb, int(max_seq_len),
                           _dtype_code(q, "q"), kv_dt, _dtype_code(out, "out"))
-    with torch.cuda.device(dev):
-        rc = raw_prefill(q.data_ptr(), q_offsets.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(),
-                         block_table.data_ptr(), seq_lens.data_ptr(),
-                         kv_scales.data_ptr() if kv_scales is not None else None, out.data_ptr(),
-                         float(softmax_scale), prob, _stream_handle(stream, dev))
-    _check(rc)
+    _launch(_lib.pda_paged_prefill_attention, index, stream, q.data_ptr(), q_offsets.data_ptr(), k_cache.data_ptr(),
+            v_cache.data_ptr(), block_table.data_ptr(), seq_lens.data_ptr(),
+            kv_scales.data_ptr() if kv_scales is not None else None, out.data_ptr(), float(softmax_scale), prob)
     return out
 
 

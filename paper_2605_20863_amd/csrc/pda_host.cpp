@@ -269,11 +269,12 @@ std::map<int, DeviceInfo> g_devices;
 std::map<std::pair<int, hipStream_t>, std::unique_ptr<Workspace>> g_workspaces;
 std::map<std::tuple<int, int, int, int, int>, int> g_occupancy;
 
-int device_info(int dev, DeviceInfo* out) {
+// *out stays valid: entries are never erased.
+int device_info(int dev, const DeviceInfo** out) {
   std::lock_guard<std::mutex> lk(g_mu);
   auto it = g_devices.find(dev);
   if (it != g_devices.end()) {
-    *out = it->second;
+    *out = &it->second;
     return PDA_OK;
   }
   DeviceInfo d;
@@ -283,8 +284,7 @@ int device_info(int dev, DeviceInfo* out) {
   d.cus = prop.multiProcessorCount;
   d.arch = prop.gcnArchName;
   d.ok = d.arch.rfind("gfx950", 0) == 0;
-  g_devices[dev] = d;
-  *out = d;
+  *out = &(g_devices[dev] = d);
   return PDA_OK;
 }
 
@@ -447,9 +447,9 @@ int run(const void* q, const void* k_cache, const void* v_cache, const int32_t* 
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return fail_hip(e, "hipGetDevice");
-  DeviceInfo di;
+  const DeviceInfo* di = nullptr;
   if ((rc = device_info(dev, &di)) != PDA_OK) return rc;
-  if (!di.ok) return fail(PDA_EUNSUPPORTED, "device %d is %s; this library is built for gfx950", dev, di.arch.c_str());
+  if (!di->ok) return fail(PDA_EUNSUPPORTED, "device %d is %s; this library is built for gfx950", dev, di->arch.c_str());
 
   int wpc = plan.waves_per_cu;
   if (wpc == 0) {
@@ -457,7 +457,7 @@ int run(const void* q, const void* k_cache, const void* v_cache, const int32_t* 
     if ((rc = occupancy(dev, plan.variant, plan.kv, problem->head_dim, plan.G, wide, &wpc)) != PDA_OK) return rc;
     if (wpc > kDefaultWavesPerCu) wpc = kDefaultWavesPerCu;
   }
-  const int waves = di.cus * wpc;
+  const int waves = di->cus * wpc;
   const int chunks_max = waves * plan.chunks_per_wave;
   const Layout lay = workspace_layout(problem, plan, gr, chunks_max);
 
@@ -538,7 +538,7 @@ int run(const void* q, const void* k_cache, const void* v_cache, const int32_t* 
   a.ws_m = reinterpret_cast<float*>(base + lay.m);
   a.ws_l = reinterpret_cast<float*>(base + lay.l);
   a.ws_acc = reinterpret_cast<float*>(base + lay.acc);
-  a.short_parts = short_parts(problem, plan, gr, options, di.cus, chunks_max);
+  a.short_parts = short_parts(problem, plan, gr, options, di->cus, chunks_max);
   // calls that overlap on the fixed scratch race; their counts must not outlive them
   a.short_clear = fixed_scratch;
   if (gr.on && (e = pda::launch_prefix(a, gr.num_groups, stream)) != hipSuccess)
@@ -583,10 +583,10 @@ int append_run(const void* k_new, const void* v_new, void* k_cache, void* v_cach
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return fail_hip(e, "hipGetDevice");
-  DeviceInfo di;
+  const DeviceInfo* di = nullptr;
   int rc;
   if ((rc = device_info(dev, &di)) != PDA_OK) return rc;
-  if (!di.ok) return fail(PDA_EUNSUPPORTED, "device %d is %s; this library is built for gfx950", dev, di.arch.c_str());
+  if (!di->ok) return fail(PDA_EUNSUPPORTED, "device %d is %s; this library is built for gfx950", dev, di->arch.c_str());
   Workspace* ws = workspace_for(dev, stream);
   std::lock_guard<std::mutex> lk(ws->mu);
   if ((rc = ensure_workspace(ws, align_up(pda::kHdrWords * 4), stream)) != PDA_OK) return rc;
@@ -698,10 +698,10 @@ int prefill_run(const void* q, const int32_t* q_offsets, const void* k_cache, co
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return fail_hip(e, "hipGetDevice");
-  DeviceInfo di;
+  const DeviceInfo* di = nullptr;
   int rc;
   if ((rc = device_info(dev, &di)) != PDA_OK) return rc;
-  if (!di.ok) return fail(PDA_EUNSUPPORTED, "device %d is %s; this library is built for gfx950", dev, di.arch.c_str());
+  if (!di->ok) return fail(PDA_EUNSUPPORTED, "device %d is %s; this library is built for gfx950", dev, di->arch.c_str());
   Workspace* ws = workspace_for(dev, stream);
   std::lock_guard<std::mutex> lk(ws->mu);
   const int len_cap = pr->max_seq_len > 0 ? pr->max_seq_len : (int)table_tokens;
@@ -715,9 +715,9 @@ int prefill_run(const void* q, const int32_t* q_offsets, const void* k_cache, co
   // has at most 2 * wgs / Hkv, and never more than every tile cut to the
   // fewest pairs. No split where the longest cache has no room for one.
   const int64_t most_cut = ((int64_t)len_cap / 32 + 1 + pda::kPfSplitPairs - 1) / pda::kPfSplitPairs;
-  int64_t slots = 2 * (((int64_t)di.cus + pr->num_kv_heads - 1) / pr->num_kv_heads) + 2;
+  int64_t slots = 2 * (((int64_t)di->cus + pr->num_kv_heads - 1) / pr->num_kv_heads) + 2;
   if (slots > items_max * most_cut) slots = items_max * most_cut;
-  if (items_max * pr->num_kv_heads > (int64_t)pda::kPfSplitUnits * di.cus || items_max > pda::kPfSplitTiles ||
+  if (items_max * pr->num_kv_heads > (int64_t)pda::kPfSplitUnits * di->cus || items_max > pda::kPfSplitTiles ||
       pr->num_seqs > pda::kPfSplitSeqs || most_cut < 2)
     slots = 0;
   const int64_t cols = slots * pr->num_kv_heads * pda::kPfColumns;
@@ -779,7 +779,7 @@ int prefill_run(const void* q, const int32_t* q_offsets, const void* k_cache, co
   a.len_shift = shift;
   a.items_max = (int32_t)items_max;
   a.out_bf16 = pr->out_dtype == PDA_DTYPE_BF16;
-  a.cus = di.cus;
+  a.cus = di->cus;
   a.nq = std::gcd(a.Hkv, 8);
   a.hdr = reinterpret_cast<int32_t*>(base);
   a.items = reinterpret_cast<int4*>(base + items_off);
