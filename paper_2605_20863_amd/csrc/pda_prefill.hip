@@ -1269,8 +1269,9 @@ __global__ __launch_bounds__(kMergeThreads) void prefill_merge_kernel(PrefillArg
         const int64_t p = at + (live ? i + k : i) * stride;
         ml[k] = a.part_ml[p];
         x[k] = *reinterpret_cast<const f32x4*>(a.part_acc + p * D + 4 * dl);
-        if (!live) ml[k] = float2{kNegInf, 0.f};
+        if (!live) ml[k].x = kNegInf;  // not folded in
       }
+      __builtin_amdgcn_sched_barrier(0);  // all the batch's loads before the first wait
       float mc = M;
 #pragma unroll
       for (int k = 0; k < kMergeBatch; ++k) mc = fmaxf(mc, ml[k].x);
@@ -1280,6 +1281,7 @@ __global__ __launch_bounds__(kMergeThreads) void prefill_merge_kernel(PrefillArg
       acc *= f;
 #pragma unroll
       for (int k = 0; k < kMergeBatch; ++k) {
+        if (i + k >= t.w) break;
         const float wgt = fast_exp2(ml[k].x - ms);
         den = __builtin_fmaf(wgt, ml[k].y, den);
 #pragma unroll
