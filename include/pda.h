@@ -380,9 +380,9 @@ typedef struct pda_prefill_problem {
  * the P . V product as fp16 (11 significant bits; bf16 V converts exactly),
  * accumulated in fp32. A live V value beyond +-65504 saturates (status bit 16).
  *
- * Image: a call of 8 or more query tiles (of 256 / G tokens) per sequence on
- * average (PDA_PREFILL_IMAGE_MIN_TILES in the environment, read on every call,
- * sets another number) first converts every cache tile that its sequences read
+ * Image: a call of 10 or more query tiles (of 256 / G tokens) per sequence on
+ * average, 13 for an fp8 cache (PDA_PREFILL_IMAGE_MIN_TILES in the environment,
+ * read on every call, sets another number) first converts every cache tile that its sequences read
  * into the stream's workspace, in the products' operand types (V to fp16, and
  * for an fp8 cache K codes to bf16), indexed like the cache; the attention
  * kernel then copies tiles from that image straight into LDS. The image takes

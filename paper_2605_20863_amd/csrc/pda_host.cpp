@@ -625,13 +625,14 @@ int64_t prefill_image_cap() {
 
 // Query tiles per sequence (the call's average) from which a prefill writes
 // the image: PDA_PREFILL_IMAGE_MIN_TILES (read on each call; 0 writes it
-// whenever it fits), kPfImageTiles by default.
-int64_t prefill_image_tiles() {
+// whenever it fits), by default where both ways take the same time.
+int64_t prefill_image_tiles(bool fp8) {
+  const int by_default = fp8 ? pda::kPfImageTilesFp8 : pda::kPfImageTilesBf16;
   const char* v = std::getenv("PDA_PREFILL_IMAGE_MIN_TILES");
-  if (!v || !*v) return pda::kPfImageTiles;
+  if (!v || !*v) return by_default;
   char* end = nullptr;
   const long long n = std::strtoll(v, &end, 10);
-  return end == v || n < 0 || n > INT32_MAX ? pda::kPfImageTiles : (int64_t)n;
+  return end == v || n < 0 || n > INT32_MAX ? by_default : (int64_t)n;
 }
 
 int prefill_run(const void* q, const int32_t* q_offsets, const void* k_cache, const void* v_cache,
@@ -732,13 +733,16 @@ int prefill_run(const void* q, const int32_t* q_offsets, const void* k_cache, co
   const int64_t img_half = pr->num_blocks * pr->num_kv_heads * (int64_t)pda::kBlockSize * pr->head_dim * 2;
   const int64_t img_bytes = kd == PDA_DTYPE_FP8_E4M3 ? 2 * img_half : img_half;
   const bool cap = capturing(stream);
-  // The image pays where several tiles read what it converts once. Measured
-  // (image against converting in the kernel, us per call, bf16 / fp8 caches, 32
-  // query and 8 KV heads): one tile per sequence, 64 sequences of 2k tokens 355
-  // against 222 / 417 against 218; 8 tiles per sequence, one of 16k tokens 211
-  // against 205 / 216 against 211; 16 tiles 344 against 354 / 354 against 369.
+  // The image pays where several tiles read what it converts once; an fp8
+  // cache's takes twice the work. Measured (image against converting in the
+  // kernel, us per call, 32 query and 8 KV heads, bf16 / fp8): 64 new tokens of
+  // 64 sequences of 2k (1 tile each) 355 against 222 / 417 against 218; 512 of 8
+  // sequences of 4k (8 tiles) 339 against 334 / 378 against 352; 1,024 of them
+  // (16) 573 against 596 / 621 against 621; every token (63) 1,415 against 1,549
+  // / 1,470 against 1,651; 28 / 4 heads, 512 of 8 x 4k (15) 298 against 326 / 332
+  // against 345.
   bool use_img = img_bytes <= prefill_image_cap() &&
-                 pr->num_tokens / TQ >= prefill_image_tiles() * pr->num_seqs;
+                 pr->num_tokens / TQ >= prefill_image_tiles(kd == PDA_DTYPE_FP8_E4M3) * pr->num_seqs;
   int64_t base_bytes = slots ? split_bytes : plain_bytes;
   if (cap && ws->bytes < base_bytes) slots = 0, base_bytes = plain_bytes;
   if (use_img && cap && ws->bytes < align_up(base_bytes) + img_bytes) use_img = false;
@@ -784,7 +788,7 @@ int prefill_run(const void* q, const int32_t* q_offsets, const void* k_cache, co
   a.hdr = reinterpret_cast<int32_t*>(base);
   a.items = reinterpret_cast<int4*>(base + items_off);
   a.slots = (int32_t)slots;
-  a.wgs = 0;  // the launcher's
+  a.wgs = a.img_shift = 0;  // the launcher's
   a.parts = reinterpret_cast<int4*>(base + parts_off);
   a.splits = reinterpret_cast<int4*>(base + splits_off);
   a.part_ml = reinterpret_cast<float2*>(base + ml_off);

@@ -134,7 +134,8 @@ constexpr int kPfBuckets = 2048; // length classes of the plan's counting sort
 constexpr int kPfSplitUnits = 8;
 constexpr int kPfSplitTiles = 2048;
 constexpr int kPfSplitSeqs = 1024;
-constexpr int kPfImageTiles = 8;   // query tiles per sequence from which the image is written
+// query tiles per sequence (the call's average) from which the image is written
+constexpr int kPfImageTilesBf16 = 10, kPfImageTilesFp8 = 13;
 constexpr int kPfSplitPairs = 16;  // fewest 32-key pairs a split makes per item
 
 struct PrefillArgs {
@@ -178,6 +179,7 @@ struct PrefillArgs {
   int4* splits;         // [slots / 2]
   float2* part_ml;      // [slots, Hkv, kPfColumns] running max (base 2), denominator
   float* part_acc;      // [slots, Hkv, kPfColumns, D]
+  int32_t img_shift;    // table entries per image workgroup: 1 << img_shift
 };
 
 hipError_t launch_prefill(const PrefillArgs& a, KvType kv, hipStream_t s);

@@ -22,7 +22,7 @@
 //   plan cuts a tile's keys into several items; each writes its unnormalised
 //   output and softmax state, and a merge kernel combines them. Measured, 512
 //   tokens over 16,182 cached ones, 28 / 4 heads, bf16: 462 us per call whole,
-//   155 us split (prep 18, attention 120, merge 8); 64-token turns of 16
+//   146 us split (prep 9, attention 120, merge 8); 64-token turns of 16
 //   sequences over an fp8 cache, 32 / 8 heads: 234 against 178.
 // * Attention kernel: a persistent grid, one workgroup (8 waves, 2 per SIMD)
 //   per CU, that takes (item, KV head) units from queues, so a CU goes from one
@@ -42,8 +42,9 @@
 //   other two buffers. On the image path they go straight from memory to LDS
 //   (global_load_lds, two 16-byte pieces per lane and pair, no registers and
 //   no conversion instructions); on the staging path (few tiles to share what
-//   an image converts, or an image larger than the host allows) each thread loads its pieces into registers, converts them and
-//   writes them to LDS between the step's two pairs.
+//   an image converts, or an image larger than the host allows) each thread
+//   loads its pieces into registers, converts them and writes them to LDS
+//   between the step's two pairs.
 // * Key order: lane group c (lanes 16c .. 16c + 15) holds keys 8c .. 8c + 7 of
 //   a pair in its score and P^T registers, 8 consecutive tokens of one block,
 //   so a 16-byte V operand is one 16-byte piece of a cached dim row.
@@ -159,8 +160,11 @@ __device__ PfSeq pf_seq(const PrefillArgs& a, int b, int& status, bool& bad) {
 struct PfPlanLds {
   int cursor[kPfBuckets];
   int wave_sum[kPlanThreads / 64];
-  // split plan only: each sequence's first q row, queries and length; each
-  // tile's sequence, index in it and pairs; sums
+};
+
+// the split plan's: also each sequence's first q row, queries and length; each
+// tile's sequence, index in it and pairs; sums
+struct PfSplitLds : PfPlanLds {
   int q0[kPfSplitSeqs], n[kPfSplitSeqs], L[kPfSplitSeqs];
   int tile_b[kPfSplitTiles], tile_t[kPfSplitTiles], tile_p[kPfSplitTiles];
   unsigned long long pairs;
@@ -259,7 +263,7 @@ __device__ __forceinline__ float pf_estimate(const PrefillArgs& a, float share, 
   return fmaxf((float)longest, share) + kUnitPairs * units / wgs + 0.5f * (float)longest;
 }
 
-__device__ void pf_plan_split(const PrefillArgs& a, PfPlanLds& lds) {
+__device__ void pf_plan_split(const PrefillArgs& a, PfSplitLds& lds) {
   const int tid = (int)threadIdx.x;
   const int l = lane_id(), wave = tid >> 6;
   if (tid == 0) {
@@ -386,13 +390,14 @@ __device__ void pf_plan_split(const PrefillArgs& a, PfPlanLds& lds) {
   if (status) atomicOr(a.hdr + kHdrStatus, status);
 }
 
-__device__ void pf_plan(const PrefillArgs& a) {
-  __shared__ PfPlanLds lds;
+template <bool SPLIT>
+__device__ __forceinline__ void pf_plan(const PrefillArgs& a) {
+  __shared__ typename std::conditional<SPLIT, PfSplitLds, PfPlanLds>::type lds;
   const int tid = (int)threadIdx.x;
   for (int i = tid; i < kPfBuckets; i += kPlanThreads) lds.cursor[i] = 0;
   if (tid < 8) a.hdr[kHdrPfQueue + tid] = 0;
   __syncthreads();
-  if (a.slots > 0) pf_plan_split(a, lds);
+  if constexpr (SPLIT) pf_plan_split(a, lds);
   else pf_plan_tiles(a, lds);
 }
 
@@ -494,10 +499,14 @@ __device__ __forceinline__ u32x4 fp8x8_to_bf16(u32x2 x) {
   return u32x4{a0.x, a0.y, a1.x, a1.y};
 }
 
-constexpr int kImgBlocks = 16;  // table entries per image workgroup
+// Table entries per image workgroup: 16, fewer where the call then has less than
+// two workgroups per compute unit. With 16 always, the prep kernel of one 16,182
+// token sequence (4 KV heads, 64 workgroups) took 18 us, now 9; a 400-token prompt
+// (32 / 8 heads) took 49 us in all (bf16; fp8 55), now 30 (31).
+constexpr int kImgShift = 4;
 constexpr int kImgBatch = 4;    // pieces a thread loads before it converts and stores them
 
-// Image workgroup g: table entries kImgBlocks * (g % cps) + 0 .. kImgBlocks - 1
+// Image workgroup g: n = 1 << img_shift table entries from n * (g % cps) on
 // of sequence g / cps. Every tile (all KV heads) of a block that a sequence
 // with queries reads, keys 0 .. L_b - 1, is converted to the image, indexed
 // like the cache (block * Hkv + KV head); blocks shared by several sequences
@@ -507,15 +516,16 @@ constexpr int kImgBatch = 4;    // pieces a thread loads before it converts and 
 template <KvType KV, int D>
 __device__ void pf_image(const PrefillArgs& a, int g) {
   using C = PfCfg<KV, D>;
-  const int cps = (a.max_blocks + kImgBlocks - 1) / kImgBlocks;
+  const int blocks = 1 << a.img_shift;
+  const int cps = (a.max_blocks + blocks - 1) >> a.img_shift;
   const int b = g / cps;
-  const int j0 = (g - b * cps) * kImgBlocks;
+  const int j0 = (g - b * cps) << a.img_shift;
   const int o0 = a.q_offsets[b], o1 = a.q_offsets[b + 1];
   if (o0 < 0 || o1 > a.T || o1 <= o0) return;  // no queries, or offsets the plan rejects
   int L = a.seq_lens[b];
   L = L < 0 ? 0 : (L > a.len_cap ? a.len_cap : L);
   const int nblk = (L + 15) / 16;
-  const int nb = nblk - j0 < kImgBlocks ? nblk - j0 : kImgBlocks;
+  const int nb = nblk - j0 < blocks ? nblk - j0 : blocks;
   if (nb <= 0) return;
   // a piece is 16 bytes of the cache: 8 bf16 values, or 16 fp8 codes (for V a
   // whole dim row of the block, for K 16 dims of one token)
@@ -578,13 +588,16 @@ __device__ void pf_image(const PrefillArgs& a, int g) {
   if (ovf) atomicOr(a.hdr + kHdrStatus, kStatusHalfRange);
 }
 
-__global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PrefillArgs a) { pf_plan(a); }
+template <bool SPLIT>
+__global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PrefillArgs a) {
+  pf_plan<SPLIT>(a);
+}
 
 // The plan (workgroup 0) and the image (the others) in one launch.
-template <KvType KV, int D>
+template <KvType KV, int D, bool SPLIT>
 __global__ __launch_bounds__(kPlanThreads) void prefill_prep_kernel(PrefillArgs a) {
   if (blockIdx.x == 0) {
-    pf_plan(a);
+    pf_plan<SPLIT>(a);
     return;
   }
   pf_image<KV, D>(a, (int)blockIdx.x - 1);
@@ -1313,10 +1326,15 @@ void* prefill_for_d(int D, bool img, bool split) {
   return D == 64 ? prefill_fn<KV, 64>(img, split) : prefill_fn<KV, 128>(img, split);
 }
 
-template <KvType KV>
+template <KvType KV, bool SPLIT>
 void* prep_for_d(int D) {
-  return D == 64 ? reinterpret_cast<void*>(&prefill_prep_kernel<KV, 64>)
-                 : reinterpret_cast<void*>(&prefill_prep_kernel<KV, 128>);
+  return D == 64 ? reinterpret_cast<void*>(&prefill_prep_kernel<KV, 64, SPLIT>)
+                 : reinterpret_cast<void*>(&prefill_prep_kernel<KV, 128, SPLIT>);
+}
+
+void* prep_fn(KvType kv, int D, bool split) {
+  if (kv == KvType::FP8) return split ? prep_for_d<KvType::FP8, true>(D) : prep_for_d<KvType::FP8, false>(D);
+  return split ? prep_for_d<KvType::BF16, true>(D) : prep_for_d<KvType::BF16, false>(D);
 }
 
 }  // namespace
@@ -1337,11 +1355,15 @@ hipError_t launch_prefill(const PrefillArgs& a, KvType kv, hipStream_t s) {
   wgs = wgs < need ? wgs : need;
   args.wgs = (int32_t)(wgs / 8 * 8 > 8 ? wgs / 8 * 8 : 8);
   if (img) {  // the plan and the image in one launch
-    const int64_t cps = (a.max_blocks + kImgBlocks - 1) / kImgBlocks;
-    void* prep = kv == KvType::FP8 ? prep_for_d<KvType::FP8>(a.D) : prep_for_d<KvType::BF16>(a.D);
-    e = hipLaunchKernel(prep, dim3((unsigned)(1 + a.B * cps)), dim3(kPlanThreads), params, 0, s);
+    auto per_seq = [&](int shift) { return ((int64_t)a.max_blocks + (1 << shift) - 1) >> shift; };
+    args.img_shift = kImgShift;
+    while (args.img_shift > 0 && a.B * per_seq(args.img_shift) < 2 * a.cus) --args.img_shift;
+    const int64_t cps = per_seq(args.img_shift);
+    e = hipLaunchKernel(prep_fn(kv, a.D, a.slots > 0), dim3((unsigned)(1 + a.B * cps)), dim3(kPlanThreads), params, 0, s);
   } else {
-    e = hipLaunchKernel(reinterpret_cast<void*>(&prefill_plan_kernel), dim3(1), dim3(kPlanThreads), params, 0, s);
+    void* plan = a.slots > 0 ? reinterpret_cast<void*>(&prefill_plan_kernel<true>)
+                             : reinterpret_cast<void*>(&prefill_plan_kernel<false>);
+    e = hipLaunchKernel(plan, dim3(1), dim3(kPlanThreads), params, 0, s);
   }
   if (e != hipSuccess) return e;
   if ((e = hipLaunchKernel(fn, dim3((unsigned)args.wgs), dim3(kPfThreads), params, 0, s)) != hipSuccess) return e;
