@@ -150,7 +150,9 @@ typedef struct pda_plan_info {
  * allocation for the graph until pda_release_workspaces(), after which no
  * graph captured before may be replayed. A graph works in the workspace of the
  * stream it was captured on: its replays must not overlap each other, calls on
- * that stream, or other graphs captured on it. This holds for every call below.
+ * that stream, or other graphs captured on it. What overlapping calls write is
+ * undefined; a later call that overlaps none is not affected. This holds for
+ * every call below.
  *
  * Errors: all argument checks run on the host before any HIP call, so invalid
  * arguments return PDA_EINVAL / PDA_EUNSUPPORTED without touching a device.

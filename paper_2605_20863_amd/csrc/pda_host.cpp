@@ -23,7 +23,6 @@
 #include <utility>
 #include <vector>
 
-static_assert(pda::kHdrWords * 4 <= 256, "the header's room in every workspace layout");
 static_assert(pda::kScratchBytes == PDA_NOALLOC_SCRATCH_BYTES, "fixed scratch size differs from the header's");
 
 namespace {
@@ -241,8 +240,11 @@ struct DeviceInfo {
 
 struct Workspace {
   std::mutex mu;
-  void* ptr = nullptr;
+  void* ptr = nullptr;  // `bytes` usable bytes; the short decode's arrival counts lie right before
   int64_t bytes = 0;
+  uint32_t epoch = 0;  // of the last short decode made outside capture
+  // the capture whose graph clears the captured calls' counts already (0: none)
+  unsigned long long cleared_in = 0;
   // The combine kernel zeroes the chunk counter after each decode kernel; if a
   // combine launch failed, the next call zeroes it first.
   bool rearm = false;
@@ -323,6 +325,15 @@ bool capturing(hipStream_t s) {
   return hipStreamIsCapturing(s, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
 }
 
+// Identifies the capture that `s` records into (0 if it cannot be told).
+unsigned long long capture_id(hipStream_t s) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  unsigned long long id = 0;
+  return hipStreamGetCaptureInfo(s, &cs, &id) == hipSuccess ? id : 0;
+}
+
+hipError_t free_workspace(void* ptr) { return hipFree(static_cast<char*>(ptr) - pda::kShortCountBytes); }
+
 // Grow ws (caller holds ws->mu) to at least `bytes`; growth waits for `s`.
 int ensure_workspace(Workspace* ws, int64_t bytes, hipStream_t s) {
   const bool cap = capturing(s);
@@ -339,19 +350,22 @@ int ensure_workspace(Workspace* ws, int64_t bytes, hipStream_t s) {
       ws->retired.push_back(ws->ptr);
     } else {
       if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
-      if ((e = hipFree(ws->ptr)) != hipSuccess) return fail_hip(e, "hipFree");
+      if ((e = free_workspace(ws->ptr)) != hipSuccess) return fail_hip(e, "hipFree");
     }
     ws->ptr = nullptr;
     ws->bytes = 0;
   }
   const int64_t want = bytes + bytes / 4;  // headroom so small growth does not reallocate
-  if ((e = hipMalloc(&ws->ptr, (size_t)want)) != hipSuccess) {
-    ws->ptr = nullptr;
+  void* p = nullptr;
+  if ((e = hipMalloc(&p, (size_t)(pda::kShortCountBytes + want))) != hipSuccess) {
     return fail(PDA_ENOMEM, "hipMalloc(%lld) of the workspace: %s", (long long)want, hipGetErrorString(e));
   }
+  ws->ptr = static_cast<char*>(p) + pda::kShortCountBytes;
   ws->bytes = want;
   ws->rearm = false;
-  if ((e = hipMemsetAsync(ws->ptr, 0, pda::kHdrWords * 4, s)) != hipSuccess) return fail_hip(e, "hipMemsetAsync");
+  ws->cleared_in = 0;
+  if ((e = hipMemsetAsync(p, 0, pda::kShortCountBytes + pda::kHdrWords * 4, s)) != hipSuccess)
+    return fail_hip(e, "hipMemsetAsync");
   return PDA_OK;
 }
 
@@ -464,6 +478,7 @@ int run(const void* q, const void* k_cache, const void* v_cache, const int32_t* 
   std::unique_lock<std::mutex> lk;
   char* base = nullptr;
   bool* rearm = nullptr;
+  Workspace* ws = nullptr;  // the stream's; null with the fixed scratch
   if (fixed_scratch) {
     if (dev < 0 || dev >= kMaxDevices) return fail(PDA_EUNSUPPORTED, "device %d: at most %d devices", dev, kMaxDevices);
     if (lay.total > pda::kScratchBytes)
@@ -478,10 +493,10 @@ int run(const void* q, const void* k_cache, const void* v_cache, const int32_t* 
       if ((e = pda::scratch_address(&p)) != hipSuccess) return fail_hip(e, "hipGetSymbolAddress(scratch)");
       fs->ptr = p;
     }
-    base = static_cast<char*>(fs->ptr);
+    base = static_cast<char*>(fs->ptr) + pda::kShortCountBytes;
     rearm = &fs->rearm;
   } else {
-    Workspace* ws = workspace_for(dev, stream);
+    ws = workspace_for(dev, stream);
     lk = std::unique_lock<std::mutex>(ws->mu);
     if ((rc = ensure_workspace(ws, lay.total, stream)) != PDA_OK) return rc;
     base = static_cast<char*>(ws->ptr);
@@ -539,8 +554,28 @@ int run(const void* q, const void* k_cache, const void* v_cache, const int32_t* 
   a.ws_l = reinterpret_cast<float*>(base + lay.l);
   a.ws_acc = reinterpret_cast<float*>(base + lay.acc);
   a.short_parts = short_parts(problem, plan, gr, options, di->cus, chunks_max);
-  // calls that overlap on the fixed scratch race; their counts must not outlive them
-  a.short_clear = fixed_scratch;
+  a.short_epoch = 0;
+  // Arrival counts that no earlier call's can spoil: counted from this call's
+  // epoch; in a capture, whose every replay has the same arguments, from zero,
+  // which the first such call recorded into the graph writes (2 us per replay);
+  // on the fixed scratch from zero at every call, which any stream may make.
+  a.short_clear = 0;
+  if (a.short_parts > 0) {
+    if (!ws) {
+      a.short_clear = 1;
+    } else if (capturing(stream)) {
+      const unsigned long long id = capture_id(stream);
+      a.short_clear = id == 0 || id != ws->cleared_in;
+      ws->cleared_in = id;
+    } else {
+      if (++ws->epoch == 0) {  // after 2^32 calls: start again
+        if ((e = hipMemsetAsync(base - pda::kShortCountBytes, 0, pda::kShortCountBytes, stream)) != hipSuccess)
+          return fail_hip(e, "hipMemsetAsync");
+        ws->epoch = 1;
+      }
+      a.short_epoch = ws->epoch;
+    }
+  }
   if (gr.on && (e = pda::launch_prefix(a, gr.num_groups, stream)) != hipSuccess)
     return fail_hip(e, "prefix kernel launch");
   if ((e = pda::launch_decode(a, plan.variant, plan.kv, stream)) != hipSuccess)
@@ -884,7 +919,7 @@ int pda_read_device_status(hipStream_t stream) {
     std::lock_guard<std::mutex> fl(fs->mu);
     if (fs->ptr) {
       int32_t word = 0;
-      int32_t* hdr = static_cast<int32_t*>(fs->ptr) + pda::kHdrStatus;
+      int32_t* hdr = reinterpret_cast<int32_t*>(static_cast<char*>(fs->ptr) + pda::kShortCountBytes) + pda::kHdrStatus;
       if ((e = hipMemcpy(&word, hdr, 4, hipMemcpyDeviceToHost)) != hipSuccess) return fail_hip(e, "hipMemcpy");
       if (word && (e = hipMemset(hdr, 0, 4)) != hipSuccess) return fail_hip(e, "hipMemset");
       all |= word;
@@ -905,9 +940,9 @@ int pda_release_workspaces(void) {
     if (!ws->ptr && ws->retired.empty()) continue;
     hipError_t e = hipSetDevice(kv.first.first);
     if (e == hipSuccess) e = hipDeviceSynchronize();
-    if (e == hipSuccess && ws->ptr) e = hipFree(ws->ptr);
+    if (e == hipSuccess && ws->ptr) e = free_workspace(ws->ptr);
     for (void* p : ws->retired)
-      if (e == hipSuccess) e = hipFree(p);
+      if (e == hipSuccess) e = free_workspace(p);
     if (e != hipSuccess) rc = fail_hip(e, "releasing a workspace");
     ws->ptr = nullptr;
     ws->bytes = 0;

@@ -39,15 +39,24 @@ constexpr int kHdrNext = 2;   // chunk counter of a dynamic split; zero between 
 constexpr int kHdrItems = 3;  // prefill: work items the plan kernel listed
 constexpr int kHdrSplits = 4; // prefill: tiles whose keys the plan split over several items
 constexpr int kHdrPfQueue = 8;  // prefill: words 8..15, the unit counters of the attention grid's queues
-constexpr int kHdrArrived = 16; // short decode: words 16..63, a byte per unit: its parts that have arrived; zero between calls
-constexpr int kHdrWords = 64;
+constexpr int kHdrWords = 16;
 
 // Short decode (see decode_short_kernel): at most this many (sequence, KV head)
-// units, one byte of the header each, and this many parts per unit, half as
-// many with more than 16 query columns (the last workgroup of a unit reads them
-// all, four at a time).
-constexpr int kShortUnits = 4 * (kHdrWords - kHdrArrived);
+// units, and this many parts per unit, half as many with more than 16 query
+// columns (the last workgroup of a unit reads them all, four at a time).
+constexpr int kShortUnits = 192;
 constexpr int kShortParts = 32;
+// Arrival counts of a unit's parts. A call made with an epoch (the workspace's
+// call number) finds every word either at a smaller epoch, which counts as zero,
+// or at its own; a captured call, whose arguments are the same at every replay,
+// has epoch 0 and words that are zero before and after it. The words, 64 bits
+// each in a cache line of its own (32 units of 8 parts: 9.0 us per call in a HIP
+// graph with the words side by side, 8.5 apart), lie right before the
+// workspace's header: an array for calls with an epoch, then one for the others.
+constexpr int kShortCountBits = 16;  // of a count's word; its epoch in the bits above
+constexpr int kShortCountStride = 16;  // 64-bit words from one unit's to the next
+constexpr int64_t kShortCountBytes = 2 * kShortUnits * kShortCountStride * 8;
+static_assert(kShortCountBytes % 256 == 0, "the header's alignment");
 constexpr int kShortWaves = 4;  // waves per workgroup
 constexpr int kShortGroup = 4;  // consecutive steps of a unit that go to one part, one per wave
 
@@ -99,7 +108,8 @@ struct DecodeArgs {
   float* ws_l;          // [slots, Gp] softmax denominator per partial
   float* ws_acc;        // [slots, Gp, D] unnormalised output per partial
   int32_t short_parts;  // > 0: the short decode kernel, with at most this many parts per unit
-  int32_t short_clear;  // 1: clear its arrival counts first
+  uint32_t short_epoch; // of its arrival counts
+  int32_t short_clear;  // 1: clear the counts of the calls without an epoch first (host only)
 };
 
 // Number of partial-result slots one call can need: one per (unit, chunk)

@@ -499,8 +499,12 @@ __device__ __forceinline__ bf16x8 k_operand(const u32x4 (&k)[MfmaCfg<KV, D>::NK4
 }
 
 // Loads of one pair: block b0, and b1 where `two` (otherwise b0's tile again,
-// all of it masked).
-template <KvType KV, int D>
+// all of it masked). KEEP: the addresses outlive the loads, so that no load's
+// destination takes its own address register, as the compiler likes to have it
+// with few registers left. The short decode kernel of one 4,096 token sequence
+// beside seven of 64 (28 / 4 heads, bf16) took 15.1 us per call with such loads
+// and 13.2 without.
+template <KvType KV, int D, bool KEEP>
 __device__ __forceinline__ void mfma_load(MfmaPair<KV, D>& bf, const DecodeArgs& a, const Blk& b0, bool two,
                                           const Blk& b1) {
   using C = MfmaCfg<KV, D>;
@@ -541,6 +545,7 @@ __device__ __forceinline__ void mfma_load(MfmaPair<KV, D>& bf, const DecodeArgs&
   const uint8_t* vt = vc + vtile * TILE + (r * kBlockSize + 8 * (c & 1)) * C::ESZ;
 #pragma unroll
   for (int m = 0; m < C::MT; ++m) bf.v[m] = ld_stream<VSlice<KV>>(vt + m * 16 * kBlockSize * C::ESZ);
+  if constexpr (KEEP) asm volatile("" ::"v"(kt), "v"(vt));
 }
 
 template <KvType KV, int D>
@@ -550,7 +555,7 @@ __device__ __forceinline__ void mfma_issue(MfmaPair<KV, D>& bf, const DecodeArgs
   Blk b1 = b0;
   const bool two = j0 + 1 < j_hi;
   if (two) b1 = block_at(a, ids, j0 + 1, L, kvh, status);
-  mfma_load<KV, D>(bf, a, b0, two, b1);
+  mfma_load<KV, D, false>(bf, a, b0, two, b1);
 }
 
 // Running-max slack (log2 units). The accumulators are rescaled only when a
@@ -1468,9 +1473,21 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(DecodeArgs a) 
 // Parts cross XCDs, whose L2s are separate: partials are stored and loaded at
 // agent scope (write-through and past the L2), each workgroup waits for its
 // stores before it counts itself as arrived, and no cache is flushed or
-// invalidated (with agent-scope fences 8 sequences of 1,000 took 24-30 us). The
-// count is a byte of the workspace header, zero between calls; the last
-// workgroup takes its unit's count back to zero.
+// invalidated (with agent-scope fences 8 sequences of 1,000 took 24-30 us).
+//
+// Counting must not depend on what an earlier call left: calls that overlapped
+// on one workspace (a graph replayed beside calls on the stream it was captured
+// on) spoil each other's counts, and a count that stayed wrong would keep every
+// later call from merging. So a call counts from its epoch: every workgroup
+// raises the word to it (a maximum) before it adds its arrival, whatever the word
+// held. A captured call has no epoch of its own at each replay: its words are
+// cleared where its graph first uses them, and the last workgroup takes its
+// unit's count back to zero.
+
+__device__ __forceinline__ uint64_t* short_counts(const DecodeArgs& a, bool with_epoch) {
+  uint64_t* const hdr = reinterpret_cast<uint64_t*>(a.hdr);
+  return hdr - (with_epoch ? 2 : 1) * (kShortUnits * kShortCountStride);
+}
 
 static_assert(kShortGroup == kShortWaves, "a group is a step per wave");
 constexpr int kShortBatch = 4;  // partials a thread of the last workgroup loads at a time
@@ -1551,7 +1568,7 @@ struct ShortMfma {
       int st1 = 0;
       const Blk b1 = block_of(a, i1, j0 + 1, sp.L, sp.kvh, st1);
       if (two) status |= st1;
-      mfma_load<KV, D>(bf, a, b0, two, b1);
+      mfma_load<KV, D, true>(bf, a, b0, two, b1);
     };
     MfmaPair<KV, D> b0, b1;
     if (sp.first < sp.steps) issue(b0, 0, sp.first);
@@ -1724,14 +1741,15 @@ __device__ __forceinline__ void short_body(const DecodeArgs& a) {
         __hip_atomic_store(a.ws_l + at, den[n], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
+    uint64_t* word = short_counts(a, a.short_epoch != 0) + u * kShortCountStride;
+    const uint64_t none = (uint64_t)a.short_epoch << kShortCountBits;
+    if (tid == 0) (void)__hip_atomic_fetch_max(word, none, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores have reached memory
     __syncthreads();
     if (tid == 0) {
-      int32_t* word = a.hdr + kHdrArrived + (u >> 2);
-      const int shift = 8 * (u & 3);
-      const int before = __hip_atomic_fetch_add(word, 1 << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const bool last = ((before >> shift) & 0xFF) == parts - 1;
-      if (last) __hip_atomic_fetch_sub(word, parts << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint64_t before = __hip_atomic_fetch_add(word, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const bool last = before == none + (uint64_t)(parts - 1);
+      if (last) __hip_atomic_fetch_sub(word, (uint64_t)parts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       last_lds = last;
     }
     __syncthreads();
@@ -1790,9 +1808,9 @@ __device__ __forceinline__ void short_body(const DecodeArgs& a) {
   }
 }
 
-__global__ __launch_bounds__(64) void short_clear_kernel(DecodeArgs a) {
-  const int i = kHdrArrived + (int)threadIdx.x;
-  if (i < kHdrWords) a.hdr[i] = 0;
+static_assert(kShortUnits % 64 == 0, "a thread per word");
+__global__ __launch_bounds__(kShortUnits) void short_clear_kernel(DecodeArgs a) {
+  short_counts(a, false)[threadIdx.x * kShortCountStride] = 0;
 }
 
 template <class W>
@@ -1941,7 +1959,7 @@ hipError_t launch_decode(const DecodeArgs& a, Variant v, KvType kv, hipStream_t 
   const float* scales = a.kv_scales;
   void* params[] = {&args, &q, &kc, &vc, &bt, &lens, &scales};
   if (parts && a.short_clear) {
-    const hipError_t e = hipLaunchKernel(reinterpret_cast<void*>(&short_clear_kernel), dim3(1), dim3(64), params, 0, s);
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<void*>(&short_clear_kernel), dim3(1), dim3(kShortUnits), params, 0, s);
     if (e != hipSuccess) return e;
   }
   if (parts)

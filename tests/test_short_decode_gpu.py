@@ -152,6 +152,47 @@ def test_short_decode_counts_are_zero_between_calls(lib):
     assert lib.read_device_status() == 0
 
 
+def test_short_decode_after_overlapping_calls(lib):
+    """Two graphs captured on one stream, replayed on two others beside eager
+    calls on it: the three work in one workspace, so what they write meanwhile is
+    undefined, but every later call that overlaps nothing is right again."""
+    a = W.generate(wl(28, 4, 128, "bf16"), DEV, seq_lens=[1500, 700, 2100])
+    b = W.generate(wl(8, 2, 64, "f32"), DEV, seq_lens=[900, 33, 64, 2000])
+    s, s1, s2 = (torch.cuda.Stream(DEV) for _ in range(3))
+    want, outs, graphs = {}, {}, {}
+    for key, inp in (("a", a), ("b", b)):
+        want[key] = call(lib, inp, torch.empty_like(inp.q))
+        outs[key] = torch.empty_like(inp.q)
+        with torch.cuda.stream(s):
+            call(lib, inp, outs[key])
+        graphs[key] = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graphs[key], stream=s):
+            for _ in range(8):
+                lib.paged_decode_attention(inp.q, inp.k_cache, inp.v_cache, inp.block_table, inp.seq_lens,
+                                           inp.kv_scales, outs[key], inp.softmax_scale,
+                                           max_seq_len=inp.layout.max_seq_len)
+    for r in range(5):
+        print(f"[short] overlap {r}", flush=True)
+        for _ in range(4):
+            with torch.cuda.stream(s1):
+                graphs["a"].replay()
+            with torch.cuda.stream(s2):
+                graphs["b"].replay()
+            with torch.cuda.stream(s):
+                lib.paged_decode_attention(a.q, a.k_cache, a.v_cache, a.block_table, a.seq_lens, a.kv_scales,
+                                           torch.empty_like(a.q), a.softmax_scale, max_seq_len=a.layout.max_seq_len)
+        torch.cuda.synchronize()
+        for key, inp in (("a", a), ("b", b)):
+            with torch.cuda.stream(s):
+                got = call(lib, inp, torch.full_like(inp.q, 7.0))
+                assert torch.equal(got, want[key]), (r, key, "eager")
+                outs[key].fill_(7.0)
+                graphs[key].replay()
+            torch.cuda.synchronize()
+            assert torch.equal(outs[key], want[key]), (r, key, "graph")
+    assert lib.read_device_status() == 0
+
+
 def test_short_decode_most_units(lib):
     """As many units as the header has counts for, each of one or two parts."""
     rng = np.random.default_rng(5)
