@@ -324,7 +324,8 @@ typedef struct pda_append_problem {
  *
  * Errors: all checks run on the host before any HIP call: PDA_EINVAL for bad
  * sizes, dtypes or NULL pointers, PDA_EUNSUPPORTED for head_dim not in {64,
- * 128} or block_size != 16. Uses the stream's workspace (status word).
+ * 128} or block_size != 16. Pointers need the alignment of their elements only
+ * (an fp8 cache may start at any byte). Uses the stream's workspace (status word).
  */
 int pda_paged_kv_append(const void* k_new,
                         const void* v_new,

@@ -29,6 +29,10 @@ constexpr float kMinScale = 0x1p-126f;
 constexpr int kAppendWaves = 4;  // waves per workgroup
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// The same in memory at any address: an fp8 cache may start at any byte, and the
+// device's unaligned accesses are as wide as its aligned ones.
+typedef u32x4 __attribute__((aligned(1))) u32x4_any;
+typedef uint32_t __attribute__((aligned(1))) u32_any;
 
 __device__ __forceinline__ int lane() { return (int)(threadIdx.x & 63); }
 
@@ -79,7 +83,7 @@ __device__ __forceinline__ void reencode_tile(uint8_t* tile, bool is_v, int o, f
 #pragma unroll
   for (int n = 0; n < N; ++n) {
     const int p = lane() + 64 * n;
-    if (p < pieces) x[n] = *reinterpret_cast<const u32x4*>(tile + 16 * p);
+    if (p < pieces) x[n] = *reinterpret_cast<const u32x4_any*>(tile + 16 * p);
   }
 #pragma unroll
   for (int n = 0; n < N; ++n) {
@@ -89,12 +93,12 @@ __device__ __forceinline__ void reencode_tile(uint8_t* tile, bool is_v, int o, f
 #pragma unroll
     for (int w = 0; w < 4; ++w) y[w] = reencode4(x[n][w], 4 * w, is_v ? o : 16, old, s);
     if (!is_v || o == 16) {
-      *reinterpret_cast<u32x4*>(tile + 16 * p) = y;
+      *reinterpret_cast<u32x4_any*>(tile + 16 * p) = y;
     } else {
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
         if (4 * w + 4 <= o) {
-          *reinterpret_cast<uint32_t*>(tile + 16 * p + 4 * w) = y[w];
+          *reinterpret_cast<u32_any*>(tile + 16 * p + 4 * w) = y[w];
         } else {
 #pragma unroll
           for (int i = 0; i < 3; ++i)

@@ -139,6 +139,34 @@ def test_append_many_steps_fp8(lib):
     assert lib.read_device_status() == 0
 
 
+@pytest.mark.parametrize("at", [1, 2, 4, 8, 13])
+@pytest.mark.parametrize("d", [64, 128])
+def test_append_fp8_cache_at_any_byte(lib, d, at):
+    """A contiguous fp8 cache that starts `at` bytes into a buffer: the same
+    bytes as in an aligned one, tokens that raise the scale at every slot."""
+    rng = np.random.default_rng(17 + at)
+    B, hkv = 16, 2
+    k, v, scales = make_cache("fp8_e4m3", B, hkv, d, rng)
+    table = np.arange(B, dtype=np.int32)[:, None]
+    positions = np.arange(B, dtype=np.int32)  # one sequence at each slot
+    kn, vn = new_values(rng, B, hkv, d, "bf16", amp=np.full((B, hkv, 1), 60.0))
+    want = gpu_append(lib, kn, vn, k, v, scales, table, positions, "fp8_e4m3")
+    got = []
+    for x in (k, v):
+        buf = torch.zeros(x.size + 64, dtype=torch.uint8, device=DEV)
+        view = buf[at:at + x.size].view(x.shape)
+        view.copy_(torch.from_numpy(x))
+        got.append((buf, view))
+    sc = torch.from_numpy(scales.copy()).to(DEV)
+    lib.paged_kv_append(kn, vn, got[0][1], got[1][1], sc, torch.from_numpy(table).to(DEV),
+                        torch.from_numpy(positions).to(DEV))
+    torch.cuda.synchronize()
+    for (buf, view), w in zip(got, want):
+        assert np.array_equal(view.cpu().numpy(), w)
+        assert not buf[:at].any() and not buf[at + w.size:].any()
+    assert np.array_equal(sc.cpu().numpy(), want[2]) and (want[2] > scales).any()
+
+
 def test_append_skips_and_flags(lib):
     rng = np.random.default_rng(31)
     B, hkv, d, NB = 5, 2, 64, 12
