@@ -27,6 +27,10 @@ namespace {
 constexpr float kE4M3Max = 448.f;
 constexpr float kMinScale = 0x1p-126f;
 constexpr int kAppendWaves = 4;  // waves per workgroup
+// Workgroups in a row of the grid. A launch has below 2^32 threads in x, which
+// one row of a workgroup per 2 pairs would reach at 2^25 (sequence, KV head)
+// pairs; the entry takes up to 2^31 - 1.
+constexpr uint32_t kAppendRow = 1u << 22;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // The same in memory at any address: an fp8 cache may start at any byte, and the
@@ -121,9 +125,9 @@ __device__ __forceinline__ void reencode_tile(uint8_t* tile, bool is_v, int o, f
 // 64 x 8 8.0 -> 4.7, 512 x 8 10.3 -> 8.5 (averages over the 16 slots of a block).
 template <KvType KV, int D>
 __global__ __launch_bounds__(64 * kAppendWaves) void append_kernel(AppendArgs a) {
-  const int w = blockIdx.x * kAppendWaves + (int)(threadIdx.x >> 6);
-  if (w >= 2 * a.B * a.Hkv) return;
-  const int pair = w >> 1;
+  const uint32_t w = (blockIdx.y * kAppendRow + blockIdx.x) * kAppendWaves + (threadIdx.x >> 6);  // below 2^32
+  if (w >= 2u * (uint32_t)a.B * (uint32_t)a.Hkv) return;
+  const int pair = (int)(w >> 1);
   const bool is_v = __builtin_amdgcn_readfirstlane(w & 1);
   const int b = pair / a.Hkv, h = pair - b * a.Hkv;
   constexpr int E = D / 64;  // elements per lane
@@ -199,7 +203,9 @@ hipError_t launch_append(const AppendArgs& a, KvType kv, hipStream_t s) {
                                   : append_for_d<KvType::FP8>(a.D);
   AppendArgs args = a;
   void* params[] = {&args};
-  return hipLaunchKernel(fn, dim3((unsigned)((waves + kAppendWaves - 1) / kAppendWaves)), dim3(64 * kAppendWaves),
+  const int64_t wgs = (waves + kAppendWaves - 1) / kAppendWaves;
+  const int64_t rows = (wgs + kAppendRow - 1) / kAppendRow;
+  return hipLaunchKernel(fn, dim3((unsigned)(rows > 1 ? kAppendRow : wgs), (unsigned)rows), dim3(64 * kAppendWaves),
                          params, 0, s);
 }
 

@@ -167,6 +167,30 @@ def test_append_fp8_cache_at_any_byte(lib, d, at):
     assert np.array_equal(sc.cpu().numpy(), want[2]) and (want[2] > scales).any()
 
 
+def test_append_more_pairs_than_one_grid_row(lib):
+    """2^25 + 5 sequences of one KV head, most of them skipped: more waves than a
+    launch's x holds. The last rows and a few in between are written."""
+    B, d = (1 << 25) + 5, 64
+    rows = [0, 3, (1 << 23) - 1, 1 << 23, (1 << 24) + 7, B - 2, B - 1]
+    kn = torch.zeros((B, 1, d), dtype=torch.bfloat16, device=DEV)
+    vn = torch.zeros_like(kn)
+    positions = torch.full((B,), -1, dtype=torch.int32, device=DEV)
+    table = torch.zeros((B, 1), dtype=torch.int32, device=DEV)
+    for i, r in enumerate(rows):
+        kn[r], vn[r] = 1 + i, 101 + i
+        positions[r], table[r, 0] = i, i
+    kc = torch.zeros((len(rows), 1, 16, d), dtype=torch.bfloat16, device=DEV)
+    vc = torch.zeros((len(rows), 1, d, 16), dtype=torch.bfloat16, device=DEV)
+    lib.paged_kv_append(kn, vn, kc, vc, None, table, positions)
+    torch.cuda.synchronize()
+    want_k, want_v = torch.zeros_like(kc), torch.zeros_like(vc)
+    for i in range(len(rows)):
+        want_k[i, 0, i] = 1 + i
+        want_v[i, 0, :, i] = 101 + i
+    assert torch.equal(kc, want_k) and torch.equal(vc, want_v)
+    assert lib.read_device_status() == 0
+
+
 def test_append_skips_and_flags(lib):
     rng = np.random.default_rng(31)
     B, hkv, d, NB = 5, 2, 64, 12
