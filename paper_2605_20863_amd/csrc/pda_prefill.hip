@@ -1043,7 +1043,12 @@ __global__ __launch_bounds__(kPfThreads) void prefill_attention(PrefillArgs a) {
     const int4 it = a.items[item];
     int4 part = make_int4(0, 0, -1, 0);
     if constexpr (SPLIT) part = a.parts[item];
-    const int b = it.x, row0 = it.y, nt = it.z, first = it.w;
+    // An item's keys, positions and block ids count from its first key, so that
+    // the pair loop is the same for whole tiles and for parts: with the first
+    // pair in the loop's indices, the fp8 image path ran 3-7% slower per pair
+    // (16,384 token prompt, 28 / 4 heads: 1,870 us per call, 1,800 like this).
+    const int base = SPLIT ? uni(32 * part.x) : 0;
+    const int b = it.x, row0 = it.y, nt = it.z, first = it.w - base;
 
     // this wave's columns: column col = 32w + 16n + r is token col / G, head col % G
     int vis[kPfNT], tokq[kPfNT];
@@ -1071,13 +1076,13 @@ __global__ __launch_bounds__(kPfThreads) void prefill_attention(PrefillArgs a) {
     const int pos_lo = uni(first + tok_lo);  // this wave's first and last query positions
     const int pos_hi = uni(first + tok_hi);
 
-    const int nkeys = first + nt > 0 ? first + nt : 0;  // keys up to the tile's last position
-    // the item's pairs [p0, npairs); p0 is a multiple of 4
-    const int p0 = SPLIT ? uni(part.x) : 0, npairs = SPLIT ? uni(part.y) : uni((nkeys + 31) / 32);
+    int nkeys = first + nt > 0 ? first + nt : 0;  // keys up to the tile's last position
+    if constexpr (SPLIT) nkeys = nkeys < 32 * (part.y - part.x) ? nkeys : 32 * (part.y - part.x);  // and to the part's end
+    const int npairs = uni((nkeys + 31) / 32);
     const int nblk = uni((nkeys + 15) / 16);
     // pairs this wave computes: those with a key at or before its last position
     const int wpairs = uni(!wave_on || pos_hi < 0 ? 0 : (pos_hi / 32 + 1 < npairs ? pos_hi / 32 + 1 : npairs));
-    const int32_t* row = a.block_table + uni64((int64_t)b * a.max_blocks);
+    const int32_t* row = a.block_table + uni64((int64_t)b * a.max_blocks + base / 16);
 
     f32x4 acc[C::MT][kPfNT];
 #pragma unroll
@@ -1125,22 +1130,22 @@ __global__ __launch_bounds__(kPfThreads) void prefill_attention(PrefillArgs a) {
     PfIds ids;
     ids.q = -1;
     ids.id = 0;
-    ids.nxt = pf_id_load(row, 64 * (p0 >> 5) + l, nblk);  // the first pair's chunk
-    pf_ids_advance(ids, row, p0 >> 5, nblk);
+    ids.nxt = pf_id_load(row, l, nblk);  // chunk 0
+    pf_ids_advance(ids, row, 0, nblk);
     PfMeta m0{1.f, 1.f, 0}, m1{1.f, 1.f, 0};
     {
-      const PfPair pa = pf_pair<KV, IMG>(a, ids, 2 * p0, nblk, nkeys, kvh, status);
-      const PfPair pb = pf_pair<KV, IMG>(a, ids, 2 * p0 + (npairs - p0 > 1 ? 2 : 0), nblk, nkeys, kvh, status);
+      const PfPair pa = pf_pair<KV, IMG>(a, ids, 0, nblk, nkeys, kvh, status);
+      const PfPair pb = pf_pair<KV, IMG>(a, ids, npairs > 1 ? 2 : 0, nblk, nkeys, kvh, status);
       if constexpr (IMG) {
-        if (npairs > p0) pf_dma<KV, D>(kimg, vimg, pa.t0, pa.t1, pl, lds0);
-        if (npairs - p0 > 1) pf_dma<KV, D>(kimg, vimg, pb.t0, pb.t1, pl, lds0 + C::BUF);
+        if (npairs > 0) pf_dma<KV, D>(kimg, vimg, pa.t0, pa.t1, pl, lds0);
+        if (npairs > 1) pf_dma<KV, D>(kimg, vimg, pb.t0, pb.t1, pl, lds0 + C::BUF);
         pf_dma_wait();
-      } else if (npairs > p0) {  // both pairs' loads before either store: one round trip
+      } else if (npairs > 0) {  // both pairs' loads before either store: one round trip
         PfStage<KV, D> sa, sb;
         pf_load<KV, D>(sa, a, pa.t0, pa.t1);
         pf_load<KV, D>(sb, a, pb.t0, pb.t1);
         pf_store<KV, D>(sa, pf_vs(pa, 0), pf_vs(pa, 1), pa.live, lds, status);
-        if (npairs - p0 > 1)
+        if (npairs > 1)
           pf_store<KV, D>(sb, pf_vs(pb, 0), pf_vs(pb, 1), pb.live, lds + C::BUF, status);
       }
       m0 = pf_meta(pa, a.scale_log2);
@@ -1157,10 +1162,7 @@ __global__ __launch_bounds__(kPfThreads) void prefill_attention(PrefillArgs a) {
       s_next[k & 1] = code;
     }
     __syncthreads();
-    // i: pairs since the item's first. The LDS buffers go by it, not by p0 + i:
-    // with p0's low bits unknown the buffer addresses cost 4-8% per pair.
-    for (int i = 0; i < npairs - p0; i += 2) {
-      const int j2 = p0 + i;
+    for (int j2 = 0; j2 < npairs; j2 += 2) {
       // blocks 2ja .. 2jb + 1 lie in one chunk of 64 (2ja is a multiple of 4, or jb = ja)
       const int ja = j2 + 2 < npairs ? j2 + 2 : npairs - 1, jb = j2 + 3 < npairs ? j2 + 3 : npairs - 1;
       pf_ids_advance(ids, row, ja >> 5, nblk);
@@ -1168,8 +1170,8 @@ __global__ __launch_bounds__(kPfThreads) void prefill_attention(PrefillArgs a) {
       const PfPair pb = pf_pair<KV, IMG>(a, ids, 2 * jb, nblk, nkeys, kvh, status);
       PfStage<KV, D> sa, sb;
       if constexpr (IMG) {
-        if (j2 + 2 < npairs) pf_dma<KV, D>(kimg, vimg, pa.t0, pa.t1, pl, lds0 + ((i + 2) & 3) * C::BUF);
-        if (j2 + 3 < npairs) pf_dma<KV, D>(kimg, vimg, pb.t0, pb.t1, pl, lds0 + ((i + 3) & 3) * C::BUF);
+        if (j2 + 2 < npairs) pf_dma<KV, D>(kimg, vimg, pa.t0, pa.t1, pl, lds0 + ((j2 + 2) & 3) * C::BUF);
+        if (j2 + 3 < npairs) pf_dma<KV, D>(kimg, vimg, pb.t0, pb.t1, pl, lds0 + ((j2 + 3) & 3) * C::BUF);
       } else {
         pf_load<KV, D>(sa, a, pa.t0, pa.t1);
         pf_load<KV, D>(sb, a, pb.t0, pb.t1);
@@ -1178,8 +1180,8 @@ __global__ __launch_bounds__(kPfThreads) void prefill_attention(PrefillArgs a) {
       if (j2 < wpairs) {
         // pair j2 + 1's K pieces are read during pair j2's P . V (even when
         // this wave skips pair j2 + 1: the buffer is in bounds)
-        const uint8_t* ba = lds + (i & 3) * C::BUF;
-        const uint8_t* bb = lds + ((i + 1) & 3) * C::BUF;
+        const uint8_t* ba = lds + (j2 & 3) * C::BUF;
+        const uint8_t* bb = lds + ((j2 + 1) & 3) * C::BUF;
 #pragma unroll
         for (int m = 0; m < C::MT; ++m) pf_kread<KV, D>(ba, o, m);
         f32x4 s0[kPfNT], s1[kPfNT];
@@ -1189,14 +1191,14 @@ __global__ __launch_bounds__(kPfThreads) void prefill_attention(PrefillArgs a) {
       const PfMeta m1cur = m1;
       if constexpr (!IMG) {
         if (j2 + 2 < npairs)
-          pf_store<KV, D>(sa, pf_vs(pa, 0), pf_vs(pa, 1), pa.live, lds + ((i + 2) & 3) * C::BUF, status);
+          pf_store<KV, D>(sa, pf_vs(pa, 0), pf_vs(pa, 1), pa.live, lds + ((j2 + 2) & 3) * C::BUF, status);
         if (j2 + 3 < npairs)
-          pf_store<KV, D>(sb, pf_vs(pb, 0), pf_vs(pb, 1), pb.live, lds + ((i + 3) & 3) * C::BUF, status);
+          pf_store<KV, D>(sb, pf_vs(pb, 0), pf_vs(pb, 1), pb.live, lds + ((j2 + 3) & 3) * C::BUF, status);
         m0 = pf_meta(pa, a.scale_log2);
         m1 = pf_meta(pb, a.scale_log2);
       }
       if (j2 + 1 < wpairs) {
-        const uint8_t* bb = lds + ((i + 1) & 3) * C::BUF;
+        const uint8_t* bb = lds + ((j2 + 1) & 3) * C::BUF;
         f32x4 s0[kPfNT], s1[kPfNT];
         pf_scores<KV, D, true>(o, qb, s0, s1, bb);
         finish(std::false_type{}, std::false_type{}, j2 + 1, s0, s1, m1cur, o, bb, bb);
@@ -1210,11 +1212,13 @@ __global__ __launch_bounds__(kPfThreads) void prefill_attention(PrefillArgs a) {
     }
     const int slot = SPLIT ? uni(part.z) : -1;
     if (SPLIT && slot >= 0) {  // part of a split tile: the unnormalised output and its softmax state
-      const int64_t col0 = ((int64_t)slot * a.Hkv + kvh) * kPfColumns + kPfWaveCols * w + r;
+      int lane = l;
+      asm volatile("" : "+v"(lane));  // addresses made here, not kept through the pair loop (they spilled)
+      const int64_t col0 = ((int64_t)slot * a.Hkv + kvh) * kPfColumns + kPfWaveCols * w + (lane & 15);
 #pragma unroll
       for (int n = 0; n < kPfNT; ++n) {
         if (tokq[n] < 0) continue;
-        float* o = a.part_acc + (col0 + 16 * n) * D + 4 * c;
+        float* o = a.part_acc + (col0 + 16 * n) * D + 4 * (lane >> 4);
 #pragma unroll
         for (int m = 0; m < C::MT; ++m) *reinterpret_cast<f32x4*>(o + 16 * m) = acc[m][n];
         if (c == 0) a.part_ml[col0 + 16 * n] = float2{rows[n].m, rows[n].l[0]};

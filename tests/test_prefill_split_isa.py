@@ -18,3 +18,11 @@ def test_split_kernels_m0(prefill_asm):  # noqa: F811
         assert [i + 1 for i in m0] == loads and all(ins[i].startswith("s_mov_b32 m0, ") for i in m0), name
     assert sum(any(s.startswith("global_load_lds") for s in ins) for ins in split.values()) == 4
     no_other_reads_of_m0(asm)
+
+
+def test_split_kernels_spill_nothing(prefill_asm):  # noqa: F811
+    """A part's slot and first key stay out of the registers of the pair loop."""
+    asm = "\n".join(re.sub(r"^(_Z\S*)split_prefill", r"\1split_prefill_kernel", line)
+                    for line in prefill_asm.splitlines())
+    for name, ins in kernels(asm).items():
+        assert not any(s.startswith(("scratch_", "buffer_store", "buffer_load")) for s in ins), name
