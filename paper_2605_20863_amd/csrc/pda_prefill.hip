@@ -162,13 +162,13 @@ struct PfPlanLds {
   int wave_sum[kPlanThreads / 64];
 };
 
-// the split plan's: also each sequence's first q row, queries and length; each
-// tile's sequence, index in it and pairs; sums
+// the split plan's: also each sequence's first q row, queries, length and tiles
+// before it; each tile's sequence, index in it and pairs; sums
 struct PfSplitLds : PfPlanLds {
-  int q0[kPfSplitSeqs], n[kPfSplitSeqs], L[kPfSplitSeqs];
+  int q0[kPfSplitSeqs], n[kPfSplitSeqs], L[kPfSplitSeqs], at[kPfSplitSeqs];
   int tile_b[kPfSplitTiles], tile_t[kPfSplitTiles], tile_p[kPfSplitTiles];
   unsigned long long pairs;
-  int tiles, longest, nsplits, nslots;
+  int longest, nsplits, nslots;
   int count[kPlanThreads / 64];
 };
 
@@ -243,9 +243,8 @@ __device__ void pf_plan_tiles(const PrefillArgs& a, PfPlanLds& lds) {
 // Split plan, for calls of few units: one 512-token chunk of a 7B-shaped model
 // is 60 units, and one long sequence among short ones keeps its units running
 // long after the others. A tile's pairs are split into
-// items of at most S pairs, a multiple of 4 (an item starts on the first LDS
-// buffer) and never below the grid's even share, so that a KV head's split items
-// stay below 2 * wgs / Hkv.
+// items of at most S pairs, a multiple of 4 and never below the grid's even
+// share, so that a KV head's split items stay below 2 * wgs / Hkv.
 //
 // S comes from an estimate of the call's time in pairs (about 0.94 us each),
 // over the 16 candidates share * (1 + k / 16): a unit costs its pairs and about
@@ -253,8 +252,10 @@ __device__ void pf_plan_tiles(const PrefillArgs& a, PfPlanLds& lds) {
 // as long as its longest unit, otherwise the even share, the units' fixed
 // costs and about half of the longest unit; a split adds the partials and the
 // merge kernel (about 8). The plan is one workgroup's chain of round trips and
-// barriers, 9 us; with the candidates counted by every thread instead of one
-// wave each it took 16.
+// barriers: 6 us for one sequence, 10 for 64. With the candidates counted by every
+// thread instead of one wave each it took 7 more, and with each wave listing its
+// sequences' tiles one sequence after the other, instead of a thread per tile
+// that looks its sequence up, 5 more for 64.
 constexpr float kUnitPairs = 7.f, kMergePairs = 8.f;
 
 __device__ __forceinline__ float pf_estimate(const PrefillArgs& a, float share, int longest, int tiles) {
@@ -268,13 +269,13 @@ __device__ void pf_plan_split(const PrefillArgs& a, PfSplitLds& lds) {
   const int l = lane_id(), wave = tid >> 6;
   if (tid == 0) {
     lds.pairs = 0;
-    lds.tiles = lds.longest = lds.nsplits = lds.nslots = 0;
+    lds.longest = lds.nsplits = lds.nslots = 0;
   }
   __syncthreads();
-  // the sequences and their places in the tile list (in any order: the list is sorted)
+  // the sequences and their places in the tile list
   int status = 0;
   bool bad = false;
-  int at = 0, tiles_b = 0;
+  int tiles_b = 0;
   static_assert(kPfSplitSeqs == kPlanThreads, "a thread per sequence");
   if (tid < a.B) {
     const PfSeq s = pf_seq(a, tid, status, bad);
@@ -282,8 +283,14 @@ __device__ void pf_plan_split(const PrefillArgs& a, PfSplitLds& lds) {
     lds.n[tid] = s.n;
     lds.L[tid] = s.L;
     tiles_b = s.tiles;
-    if (!bad && tiles_b) at = atomicAdd(&lds.tiles, tiles_b);
   }
+  int incl = tiles_b;  // within the wave; the waves before it are added below
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(incl, o, 64);
+    if (l >= o) incl += y;
+  }
+  if (l == 63) lds.count[wave] = incl;
   if (__syncthreads_or(bad)) {
     if (tid == 0) {
       a.hdr[kHdrItems] = 0;
@@ -292,26 +299,29 @@ __device__ void pf_plan_split(const PrefillArgs& a, PfSplitLds& lds) {
     }
     return;
   }
-  const int tiles = lds.tiles;
-  // each wave lists its 64 sequences' tiles, 64 tiles of one sequence at a time
-  uint64_t todo = __ballot(tiles_b > 0);
+  int tiles = 0, before = 0;
+#pragma unroll
+  for (int w = 0; w < kPlanThreads / 64; ++w) {
+    if (w == wave) before = tiles;
+    tiles += lds.count[w];
+  }
+  if (tid < a.B) lds.at[tid] = before + incl - tiles_b;
+  __syncthreads();
+  // a thread per tile: its sequence is the last that starts at or before it and has tiles
   unsigned long long pairs = 0;
   int longest = 0;
-  while (todo) {
-    const int src = __builtin_ctzll(todo);
-    todo &= todo - 1;
-    const int b = (wave << 6) + src;
-    const int nb = __builtin_amdgcn_readlane(tiles_b, src), at0 = __builtin_amdgcn_readlane(at, src);
-    const int n = lds.n[b], L = lds.L[b];
-    for (int t = l; t < nb; t += 64) {
-      const int end = (t + 1) * a.TQ;
-      const int p = pf_pairs(L - n + (end < n ? end : n));
-      lds.tile_b[at0 + t] = b;
-      lds.tile_t[at0 + t] = t;
-      lds.tile_p[at0 + t] = p;
-      pairs += (unsigned)p;
-      longest = longest > p ? longest : p;
-    }
+  for (int i = tid; i < tiles; i += kPlanThreads) {
+    int b = 0;
+#pragma unroll
+    for (int step = kPfSplitSeqs / 2; step > 0; step >>= 1)
+      if (b + step < a.B && lds.at[b + step] <= i) b += step;
+    const int t = i - lds.at[b], n = lds.n[b], end = (t + 1) * a.TQ;
+    const int p = pf_pairs(lds.L[b] - n + (end < n ? end : n));
+    lds.tile_b[i] = b;
+    lds.tile_t[i] = t;
+    lds.tile_p[i] = p;
+    pairs += (unsigned)p;
+    longest = longest > p ? longest : p;
   }
   if (pairs) {
     atomicAdd(&lds.pairs, pairs);

@@ -29,11 +29,15 @@ def path(request, monkeypatch):
 # least 16 pairs of 32 keys) -- one sequence alone; lengths around multiples of
 # a pair, a block and an item's four pairs; a long sequence among short and
 # empty ones, with more queries than keys in one
+# -- and, for the plan's list of tiles, runs of sequences without queries first,
+# last and between others, and as many sequences as it takes
 SPLITS = {
     "alone": ([5000], [70]),
     "one_token": ([3333], [1]),
     "edges": ([2047, 2048, 2049, 1024, 1025, 544, 513, 31], [5, 64, 33, 40, 17, 32, 1, 31]),
     "mixed": ([6000, 0, 20, 1, 300, 48, 5], [90, 0, 20, 1, 200, 16, 9]),
+    "without_queries": ([100, 40, 3000, 0, 9, 700, 700, 5, 60], [0, 0, 150, 0, 0, 90, 300, 0, 0]),
+    "most_sequences": ([700] + [17 + i % 30 for i in range(1023)], [60] + [i % 3 for i in range(1023)]),
 }
 
 
