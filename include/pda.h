@@ -383,12 +383,14 @@ typedef struct pda_prefill_problem {
  * the P . V product as fp16 (11 significant bits; bf16 V converts exactly),
  * accumulated in fp32. A live V value beyond +-65504 saturates (status bit 16).
  *
- * Image: a call of 10 or more query tiles (of 256 / G tokens) per sequence on
- * average, 13 for an fp8 cache (PDA_PREFILL_IMAGE_MIN_TILES in the environment,
+ * Image: a call of 5 or more query tiles (of 256 / G tokens) per sequence on
+ * average, 8 for an fp8 cache (PDA_PREFILL_IMAGE_MIN_TILES in the environment,
  * read on every call, sets another number) first converts every cache tile that its sequences read
  * into the stream's workspace, in the products' operand types (V to fp16, and
  * for an fp8 cache K codes to bf16), indexed like the cache; the attention
- * kernel then copies tiles from that image straight into LDS. The image takes
+ * kernel then copies tiles from that image straight into LDS. A call of fewer
+ * on average but 100 or more (and twice that number) in all does so for those of
+ * its sequences that have that many themselves. The image takes
  * num_blocks * num_kv_heads * 16 * head_dim * 2 bytes (twice that for an fp8
  * cache). With fewer tiles, when the image exceeds the environment variable
  * PDA_PREFILL_IMAGE_MAX_MB (MiB, read on every call; default 8192), when a
@@ -405,7 +407,8 @@ typedef struct pda_prefill_problem {
  * 16 bytes, the int32 and f32 arrays 4), or more than INT32_MAX / 8 work units
  * (tiles of 256 / G query tokens times KV heads); PDA_EUNSUPPORTED for
  * head_dim not in {64, 128}, block_size != 16, G > 16, or an f32 cache. Uses
- * the stream's workspace: 16 bytes per work item of 256 / G query tokens, the
+ * the stream's workspace: 16 bytes per work item of 256 / G query tokens (twice
+ * that where sequence by sequence decides), the
  * partials of a split (256 * (4 head_dim + 8) bytes per part, at most about two
  * parts per compute unit: 68 MB), and the image described above.
  */

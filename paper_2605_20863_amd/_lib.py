@@ -455,11 +455,13 @@ def paged_prefill_attention(q, q_offsets, k_cache, v_cache, block_table, seq_len
     q_offsets[b] .. q_offsets[b + 1] - 1 (int32 [B + 1]) are the last tokens of
     sequence b, whose cache holds seq_lens[b] tokens; cache layouts as for
     paged_decode_attention. A call of at least PDA_PREFILL_IMAGE_MIN_TILES
-    (default 10, 13 for fp8) tiles of 256 / G query tokens per sequence on average converts
+    (default 5, 8 for fp8) tiles of 256 / G query tokens per sequence on average converts
     the cache tiles it reads into an image in the stream's workspace (V as fp16,
     an fp8 cache's K as bf16; NB * Hkv * 16 * D * 2 bytes, twice that for fp8)
-    unless that exceeds PDA_PREFILL_IMAGE_MAX_MB (default 8192); otherwise the
-    kernel converts tiles in registers. The results are the same bit for bit.
+    unless that exceeds PDA_PREFILL_IMAGE_MAX_MB (default 8192); with fewer on
+    average but 100 in all it does so for the sequences that have that many;
+    otherwise the kernel converts tiles in registers. The results are the same
+    bit for bit.
     """
     tensors = {"q": q, "q_offsets": q_offsets, "k_cache": k_cache, "v_cache": v_cache,
                "block_table": block_table, "seq_lens": seq_lens, "out": out}

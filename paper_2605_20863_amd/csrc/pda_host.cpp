@@ -756,40 +756,59 @@ int prefill_run(const void* q, const int32_t* q_offsets, const void* k_cache, co
   if (items_max * pr->num_kv_heads > (int64_t)pda::kPfSplitUnits * di->cus || items_max > pda::kPfSplitTiles ||
       pr->num_seqs > pda::kPfSplitSeqs || most_cut < 2)
     slots = 0;
-  const int64_t cols = slots * pr->num_kv_heads * pda::kPfColumns;
-  const int64_t list_max = items_max + slots;  // a split adds at most its slots
-  const int64_t plain_bytes = items_off + items_max * 16;
-  const int64_t parts_off = items_off + list_max * 16;
-  const int64_t splits_off = align_up(parts_off + list_max * 16);
-  const int64_t ml_off = align_up(splits_off + slots / 2 * 16);
-  const int64_t acc_off = align_up(ml_off + cols * 8);
-  const int64_t split_bytes = acc_off + cols * pr->head_dim * 4;
   // Image: V in fp16; for an fp8 cache K in bf16 too.
   const int64_t img_half = pr->num_blocks * pr->num_kv_heads * (int64_t)pda::kBlockSize * pr->head_dim * 2;
   const int64_t img_bytes = kd == PDA_DTYPE_FP8_E4M3 ? 2 * img_half : img_half;
   const bool cap = capturing(stream);
   // The image pays where several tiles read what it converts once; an fp8
-  // cache's takes twice the work. Measured (image against converting in the
-  // kernel, us per call, 32 query and 8 KV heads, bf16 / fp8): 64 new tokens of
-  // 64 sequences of 2k (1 tile each) 355 against 222 / 417 against 218; 512 of 8
-  // sequences of 4k (8 tiles) 339 against 334 / 378 against 352; 1,024 of them
-  // (16) 573 against 596 / 621 against 621; every token (63) 1,415 against 1,549
-  // / 1,470 against 1,651; 28 / 4 heads, 512 of 8 x 4k (15) 298 against 326 / 332
-  // against 345.
-  bool use_img = img_bytes <= prefill_image_cap() &&
-                 pr->num_tokens / TQ >= prefill_image_tiles(kd == PDA_DTYPE_FP8_E4M3) * pr->num_seqs;
-  int64_t base_bytes = slots ? split_bytes : plain_bytes;
-  if (cap && ws->bytes < base_bytes) slots = 0, base_bytes = plain_bytes;
-  if (use_img && cap && ws->bytes < align_up(base_bytes) + img_bytes) use_img = false;
+  // cache's takes twice the work. Measured (image / converting in the kernel, us
+  // per call, bf16; fp8), n query tiles of each of B sequences of L cached tokens:
+  //   28 / 4 heads,  8 x 4,096: n = 2  72 /  72;  84 /  74   n = 5 141 / 159; 161 / 168
+  //                             n = 8 151 / 165; 166 / 174
+  //                 32 x 2,048: n = 2 103 /  99; 121 / 103   n = 5 225 / 229; 254 / 243
+  //                             n = 8 294 / 303; 322 / 319
+  //   32 / 8 heads, 32 x 2,048: n = 2 207 / 183; 250 / 189   n = 5 403 / 398; 450 / 405
+  //                             n = 8 544 / 559; 588 / 595   n = 16 897 / 963; 944 / 1,025
+  //
+  // The average says too little where a batch mixes long prompts with one-token
+  // rows or empty slots. With fewer tiles per sequence on average, but many in
+  // all, the call is mixed: the plan decides sequence by sequence. That is a
+  // second attention launch, 3 us if its list is empty and 10 to 25 with a few
+  // short items, for about 10% of the prompts' time: from 100 tiles on. One
+  // prompt of 8,192 beside 31 rows of one token each, converting / mixed: 28 / 4
+  // heads bf16 543 / 489, fp8 581 / 524; beside 31 rows over 2,048 tokens 582 / 542,
+  // 620 / 574. One of 2,048 (57 tiles) beside 31 rows: 94 / 98.
+  const int64_t tiles_min = prefill_image_tiles(kd == PDA_DTYPE_FP8_E4M3), tiles_all = pr->num_tokens / TQ;
+  const bool mixed = tiles_all < tiles_min * pr->num_seqs;
+  bool use_img = img_bytes <= prefill_image_cap() && (!mixed || (tiles_all >= pda::kPfMixedTiles && tiles_all >= 2 * tiles_min));
+  struct PrefillLayout {
+    int64_t list_max, parts, splits, ml, acc, img, total;
+  };
+  auto layout = [&](int64_t n, bool image) {
+    PrefillLayout w;
+    w.list_max = items_max + n;  // a split adds at most its slots
+    const int64_t lists = image && mixed ? 2 : 1, cols = n * pr->num_kv_heads * pda::kPfColumns;
+    w.parts = items_off + lists * w.list_max * 16;
+    w.splits = align_up(w.parts + lists * w.list_max * 16);
+    w.ml = align_up(w.splits + n / 2 * 16);
+    w.acc = align_up(w.ml + cols * 8);
+    w.total = n ? w.acc + cols * pr->head_dim * 4 : w.parts;
+    w.img = align_up(w.total);
+    if (image) w.total = w.img + img_bytes;
+    return w;
+  };
+  if (cap && ws->bytes < layout(slots, false).total) slots = 0;
+  if (use_img && cap && ws->bytes < layout(slots, true).total) use_img = false;
+  PrefillLayout lay;
   for (;;) {
-    rc = ensure_workspace(ws, use_img ? align_up(base_bytes) + img_bytes : base_bytes, stream);
+    lay = layout(slots, use_img);
+    rc = ensure_workspace(ws, lay.total, stream);
     if (rc != PDA_ENOMEM || !(use_img || slots)) break;
     if (use_img) use_img = false;
-    else slots = 0, base_bytes = plain_bytes;
+    else slots = 0;
     g_error.clear();
   }
   if (rc != PDA_OK) return rc;
-  const int64_t img_off = align_up(base_bytes);
   char* base = static_cast<char*>(ws->ptr);
 
   pda::PrefillArgs a;
@@ -823,13 +842,15 @@ int prefill_run(const void* q, const int32_t* q_offsets, const void* k_cache, co
   a.hdr = reinterpret_cast<int32_t*>(base);
   a.items = reinterpret_cast<int4*>(base + items_off);
   a.slots = (int32_t)slots;
+  a.list_max = (int32_t)lay.list_max;
+  a.img_tiles = use_img && mixed ? (int32_t)tiles_min : 0;
   a.wgs = a.img_shift = 0;  // the launcher's
-  a.parts = reinterpret_cast<int4*>(base + parts_off);
-  a.splits = reinterpret_cast<int4*>(base + splits_off);
-  a.part_ml = reinterpret_cast<float2*>(base + ml_off);
-  a.part_acc = reinterpret_cast<float*>(base + acc_off);
-  a.v_img = use_img ? base + img_off : nullptr;
-  a.k_img = use_img && kd == PDA_DTYPE_FP8_E4M3 ? base + img_off + img_half : nullptr;
+  a.parts = reinterpret_cast<int4*>(base + lay.parts);
+  a.splits = reinterpret_cast<int4*>(base + lay.splits);
+  a.part_ml = reinterpret_cast<float2*>(base + lay.ml);
+  a.part_acc = reinterpret_cast<float*>(base + lay.acc);
+  a.v_img = use_img ? base + lay.img : nullptr;
+  a.k_img = use_img && kd == PDA_DTYPE_FP8_E4M3 ? base + lay.img + img_half : nullptr;
   const pda::KvType kv = kd == PDA_DTYPE_BF16 ? pda::KvType::BF16 : pda::KvType::FP8;
   if ((e = pda::launch_prefill(a, kv, stream)) != hipSuccess) return fail_hip(e, "prefill kernel launch");
   return PDA_OK;
@@ -899,19 +920,16 @@ int pda_read_device_status(hipStream_t stream) {
   if ((e = hipStreamSynchronize(stream)) != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
   // the current workspace and any a captured graph still writes to
   int32_t all = 0;
-  for (void* p : ws->retired) {
-    int32_t word = 0;
-    int32_t* hdr = static_cast<int32_t*>(p) + pda::kHdrStatus;
-    if ((e = hipMemcpy(&word, hdr, 4, hipMemcpyDeviceToHost)) != hipSuccess) return fail_hip(e, "hipMemcpy");
-    if (word && (e = hipMemset(hdr, 0, 4)) != hipSuccess) return fail_hip(e, "hipMemset");
-    all |= word;
-  }
-  if (ws->ptr) {
-    int32_t word = 0;
-    int32_t* hdr = static_cast<int32_t*>(ws->ptr) + pda::kHdrStatus;
-    if ((e = hipMemcpy(&word, hdr, 4, hipMemcpyDeviceToHost)) != hipSuccess) return fail_hip(e, "hipMemcpy");
-    if (word && (e = hipMemset(hdr, 0, 4)) != hipSuccess) return fail_hip(e, "hipMemset");
-    all |= word;
+  std::vector<void*> headers = ws->retired;
+  if (ws->ptr) headers.push_back(ws->ptr);
+  for (void* p : headers) {
+    for (int half : {0, pda::kHdrStaged}) {
+      int32_t word = 0;
+      int32_t* hdr = static_cast<int32_t*>(p) + half + pda::kHdrStatus;
+      if ((e = hipMemcpy(&word, hdr, 4, hipMemcpyDeviceToHost)) != hipSuccess) return fail_hip(e, "hipMemcpy");
+      if (word && (e = hipMemset(hdr, 0, 4)) != hipSuccess) return fail_hip(e, "hipMemset");
+      all |= word;
+    }
   }
   // the device's fixed scratch, once the no-allocation entry point has used it
   if (dev >= 0 && dev < kMaxDevices) {

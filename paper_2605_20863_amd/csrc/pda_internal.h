@@ -39,7 +39,8 @@ constexpr int kHdrNext = 2;   // chunk counter of a dynamic split; zero between 
 constexpr int kHdrItems = 3;  // prefill: work items the plan kernel listed
 constexpr int kHdrSplits = 4; // prefill: tiles whose keys the plan split over several items
 constexpr int kHdrPfQueue = 8;  // prefill: words 8..15, the unit counters of the attention grid's queues
-constexpr int kHdrWords = 16;
+constexpr int kHdrStaged = 16;  // mixed prefill: words 16..31, the second list's status, items and queues
+constexpr int kHdrWords = 32;
 
 // Short decode (see decode_short_kernel): at most this many (sequence, KV head)
 // units, and this many parts per unit, half as many with more than 16 query
@@ -145,7 +146,8 @@ constexpr int kPfSplitUnits = 8;
 constexpr int kPfSplitTiles = 2048;
 constexpr int kPfSplitSeqs = 1024;
 // query tiles per sequence (the call's average) from which the image is written
-constexpr int kPfImageTilesBf16 = 10, kPfImageTilesFp8 = 13;
+constexpr int kPfImageTilesBf16 = 5, kPfImageTilesFp8 = 8;
+constexpr int kPfMixedTiles = 100;  // fewest query tiles of a mixed call
 constexpr int kPfSplitPairs = 16;  // fewest 32-key pairs a split makes per item
 
 struct PrefillArgs {
@@ -170,7 +172,12 @@ struct PrefillArgs {
   int32_t cus;          // compute units of the device
   int32_t nq;           // unit queues: gcd(Hkv, 8)
   int32_t* hdr;         // workspace header (status, item count, queue counters)
-  int4* items;          // [items_max + slots] {sequence, first q row, tokens, first position}
+  int4* items;          // [list_max] {sequence, first q row, tokens, first position}
+  int32_t list_max;     // items_max + slots
+  // > 0 (mixed): only the sequences of at least this many query tiles have their
+  // tiles in the image; the others' items are a second list right behind the
+  // first (and so are its parts), run by a launch of its own that reads the cache.
+  int32_t img_tiles;
   // Image of the cache's tiles in the products' operand types, indexed like the
   // cache (block * Hkv + KV head, 16 * D two-byte elements per tile): V in fp16
   // (v_img), and for an fp8 cache K in bf16 (k_img). v_img null: the attention
@@ -185,7 +192,7 @@ struct PrefillArgs {
   // merge kernel combines them. slots bounds the slots of one KV head.
   int32_t slots;
   int32_t wgs;          // workgroups of the attention grid
-  int4* parts;          // [items_max + slots]
+  int4* parts;          // [list_max]
   int4* splits;         // [slots / 2]
   float2* part_ml;      // [slots, Hkv, kPfColumns] running max (base 2), denominator
   float* part_acc;      // [slots, Hkv, kPfColumns, D]

@@ -160,6 +160,7 @@ __device__ PfSeq pf_seq(const PrefillArgs& a, int b, int& status, bool& bad) {
 struct PfPlanLds {
   int cursor[kPfBuckets];
   int wave_sum[kPlanThreads / 64];
+  int imaged;  // mixed calls: items of the first list
 };
 
 // the split plan's: also each sequence's first q row, queries, length and tiles
@@ -200,12 +201,32 @@ __device__ __forceinline__ void pf_bucket_starts(const PrefillArgs& a, PfPlanLds
     s.cursor[tid * PER + i] = start;
     start += v[i];
   }
-  if (tid == kPlanThreads - 1) a.hdr[kHdrItems] = start;  // total items
+  const int first = start - run;  // items before this thread's buckets
+  if (tid == kPlanThreads / 2) s.imaged = first;
   __syncthreads();
+  if (tid == kPlanThreads - 1) {  // items of each list
+    a.hdr[kHdrItems] = a.img_tiles > 0 ? s.imaged : start;
+    a.hdr[kHdrStaged + kHdrItems] = start - s.imaged;
+  }
 }
 
 // 32-key pairs of `keys` keys
 __device__ __forceinline__ int pf_pairs(int keys) { return keys > 0 ? (keys + 31) / 32 : 0; }
+
+// Mixed calls have two lists, sorted as one: the items of the sequences with n
+// query tokens enough for the image, and behind them (in the upper half of the
+// buckets, in memory a.list_max entries on) the others'.
+__device__ __forceinline__ bool pf_staged(const PrefillArgs& a, int n) { return (n + a.TQ - 1) / a.TQ < a.img_tiles; }
+
+__device__ __forceinline__ int pf_bucket(const PrefillArgs& a, int key, int n) {
+  return a.img_tiles > 0 ? key / 2 + (pf_staged(a, n) ? kPfBuckets / 2 : 0) : key;
+}
+
+// Place in memory of the item at `pos` of the sorted list, of a sequence of n
+// query tokens.
+__device__ __forceinline__ int pf_place(const PrefillArgs& a, const PfPlanLds& s, int pos, int n) {
+  return a.img_tiles > 0 && pf_staged(a, n) ? pos - s.imaged + a.list_max : pos;
+}
 
 // Offsets that are not non-decreasing within [0, T] list no item at all (status
 // bit 8): with them the sequences could overlap and overrun the list. Otherwise
@@ -217,11 +238,11 @@ __device__ void pf_plan_tiles(const PrefillArgs& a, PfPlanLds& lds) {
   bool bad = false;
   for (int b = tid; b < a.B; b += kPlanThreads) {
     const PfSeq s = pf_seq(a, b, status, bad);
-    if (s.tiles) atomicAdd(&cursor[s.key], s.tiles);
+    if (s.tiles) atomicAdd(&cursor[pf_bucket(a, s.key, s.n)], s.tiles);
   }
   if (__syncthreads_or(bad)) {
     if (tid == 0) {
-      a.hdr[kHdrItems] = 0;
+      a.hdr[kHdrItems] = a.hdr[kHdrStaged + kHdrItems] = 0;
       atomicOr(a.hdr + kHdrStatus, kStatusBadOffsets);
     }
     return;
@@ -230,7 +251,7 @@ __device__ void pf_plan_tiles(const PrefillArgs& a, PfPlanLds& lds) {
   for (int b = tid; b < a.B; b += kPlanThreads) {
     const PfSeq s = pf_seq(a, b, status, bad);
     if (!s.tiles) continue;
-    int pos = atomicAdd(&cursor[s.key], s.tiles);
+    int pos = pf_place(a, lds, atomicAdd(&cursor[pf_bucket(a, s.key, s.n)], s.tiles), s.n);
     for (int t = s.tiles - 1; t >= 0; --t) {  // the last (heaviest) tile first
       const int t0 = t * a.TQ;
       const int nt = s.n - t0 < a.TQ ? s.n - t0 : a.TQ;
@@ -293,7 +314,7 @@ __device__ void pf_plan_split(const PrefillArgs& a, PfSplitLds& lds) {
   if (l == 63) lds.count[wave] = incl;
   if (__syncthreads_or(bad)) {
     if (tid == 0) {
-      a.hdr[kHdrItems] = 0;
+      a.hdr[kHdrItems] = a.hdr[kHdrStaged + kHdrItems] = 0;
       a.hdr[kHdrSplits] = 0;
       atomicOr(a.hdr + kHdrStatus, kStatusBadOffsets);
     }
@@ -373,7 +394,7 @@ __device__ void pf_plan_split(const PrefillArgs& a, PfSplitLds& lds) {
   for (int i = tid; i < tiles; i += kPlanThreads) {
     int len;
     const int c = cut(lds.tile_p[i], len);
-    atomicAdd(&lds.cursor[key(len)], c);
+    atomicAdd(&lds.cursor[pf_bucket(a, key(len), lds.n[lds.tile_b[i]])], c);
   }
   __syncthreads();
   pf_bucket_starts(a, lds);
@@ -383,7 +404,7 @@ __device__ void pf_plan_split(const PrefillArgs& a, PfSplitLds& lds) {
     const int nt = n - t0 < a.TQ ? n - t0 : a.TQ;
     int len;
     const int c = cut(p, len);
-    int pos = atomicAdd(&lds.cursor[key(len)], c);
+    int pos = pf_place(a, lds, atomicAdd(&lds.cursor[pf_bucket(a, key(len), n)], c), n);
     int slot = -1;
     if (c > 1) {
       slot = atomicAdd(&lds.nslots, c);
@@ -405,7 +426,7 @@ __device__ __forceinline__ void pf_plan(const PrefillArgs& a) {
   __shared__ typename std::conditional<SPLIT, PfSplitLds, PfPlanLds>::type lds;
   const int tid = (int)threadIdx.x;
   for (int i = tid; i < kPfBuckets; i += kPlanThreads) lds.cursor[i] = 0;
-  if (tid < 8) a.hdr[kHdrPfQueue + tid] = 0;
+  if (tid < 8) a.hdr[kHdrPfQueue + tid] = a.hdr[kHdrStaged + kHdrPfQueue + tid] = 0;
   __syncthreads();
   if constexpr (SPLIT) pf_plan_split(a, lds);
   else pf_plan_tiles(a, lds);
@@ -532,6 +553,7 @@ __device__ void pf_image(const PrefillArgs& a, int g) {
   const int j0 = (g - b * cps) << a.img_shift;
   const int o0 = a.q_offsets[b], o1 = a.q_offsets[b + 1];
   if (o0 < 0 || o1 > a.T || o1 <= o0) return;  // no queries, or offsets the plan rejects
+  if (a.img_tiles > 0 && pf_staged(a, o1 - o0)) return;
   int L = a.seq_lens[b];
   L = L < 0 ? 0 : (L > a.len_cap ? a.len_cap : L);
   const int nblk = (L + 15) / 16;
@@ -1381,6 +1403,16 @@ hipError_t launch_prefill(const PrefillArgs& a, KvType kv, hipStream_t s) {
   }
   if (e != hipSuccess) return e;
   if ((e = hipLaunchKernel(fn, dim3((unsigned)args.wgs), dim3(kPfThreads), params, 0, s)) != hipSuccess) return e;
+  if (img && a.img_tiles > 0) {  // mixed: the second list, with the second half of the header
+    PrefillArgs staged = args;
+    staged.items += a.list_max;
+    staged.parts += a.list_max;
+    staged.hdr += kHdrStaged;
+    void* more[] = {&staged};
+    fn = kv == KvType::FP8 ? prefill_for_d<KvType::FP8>(a.D, false, a.slots > 0)
+                           : prefill_for_d<KvType::BF16>(a.D, false, a.slots > 0);
+    if ((e = hipLaunchKernel(fn, dim3((unsigned)args.wgs), dim3(kPfThreads), more, 0, s)) != hipSuccess) return e;
+  }
   if (a.slots <= 0) return hipSuccess;
   void* merge = a.D == 64 ? reinterpret_cast<void*>(&prefill_merge_kernel<64>)
                           : reinterpret_cast<void*>(&prefill_merge_kernel<128>);

@@ -34,8 +34,15 @@ class Sim:
         self.lib = ctypes.CDLL(path)
         self.lib.sim_room.restype = ctypes.c_int64
         self.lib.sim_room.argtypes = [ctypes.c_int64]
+        self.lib.sim_allocated.restype = ctypes.c_int64
         self.lib.sim_reset.argtypes = [ctypes.c_ulonglong, ctypes.c_int64]
         self.lib.pda_last_error.restype = ctypes.c_char_p
+
+    def room(self, p):
+        return self.lib.sim_room(p)
+
+    def allocated(self):
+        return self.lib.sim_allocated()
 
     def reset(self, capture=0, limit=-1):
         self.lib.sim_reset(capture, limit)
@@ -61,7 +68,8 @@ class Sim:
         p = ctypes.c_void_p(0x10000)
         rc = self.lib.pda_paged_prefill_attention(p, p, p, p, p, p, p, p, ctypes.c_float(0.1), ctypes.byref(pr),
                                                   ctypes.c_void_p(stream))
-        return rc, self._notes(self.lib.sim_prefill, "slots", "v_img", "k_img")
+        return rc, self._notes(self.lib.sim_prefill, "slots", "v_img", "k_img", "img_tiles", "list_max", "hdr", "items",
+                               "parts", "splits", "part_ml", "part_acc")
 
     def release(self):
         self.lib.pda_release_workspaces()

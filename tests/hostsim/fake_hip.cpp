@@ -19,6 +19,7 @@ char g_scratch[pda::kShortCountBytes + pda::kScratchBytes];
 pda::DecodeArgs g_decode;
 pda::PrefillArgs g_prefill;
 int g_launches = 0;
+int64_t g_last = 0;
 }  // namespace
 
 extern "C" {
@@ -38,9 +39,19 @@ void sim_decode(int64_t* out) {
 // the last prefill launch
 void sim_prefill(int64_t* out) {
   out[0] = g_prefill.slots;
-  out[1] = g_prefill.v_img != nullptr;
-  out[2] = g_prefill.k_img != nullptr;
+  out[1] = (int64_t)g_prefill.v_img;
+  out[2] = (int64_t)g_prefill.k_img;
+  out[3] = g_prefill.img_tiles;
+  out[4] = g_prefill.list_max;
+  out[5] = (int64_t)g_prefill.hdr;
+  out[6] = (int64_t)g_prefill.items;
+  out[7] = (int64_t)g_prefill.parts;
+  out[8] = (int64_t)g_prefill.splits;
+  out[9] = (int64_t)g_prefill.part_ml;
+  out[10] = (int64_t)g_prefill.part_acc;
 }
+// bytes of the last allocation
+int64_t sim_allocated(void) { return g_last; }
 // usable bytes from p to the end of its allocation, -1 if it lies in none
 int64_t sim_room(int64_t p) {
   for (auto& [base, size] : g_sizes)
@@ -62,6 +73,7 @@ hipError_t hipMalloc(void** p, size_t n) {
   if (g_capture) return hipErrorStreamCaptureUnsupported;
   if (!(*p = std::calloc(1, n))) return hipErrorOutOfMemory;
   g_sizes[*p] = n;
+  g_last = (int64_t)n;
   return hipSuccess;
 }
 hipError_t hipFree(void* p) {
