@@ -198,6 +198,7 @@ def test_graph_prefill_capture_falls_back_to_staging(lib, monkeypatch, kv):
                                     c.kv_scales, out, c.softmax_scale, max_seq_len=c.layout.max_seq_len)
 
     s = torch.cuda.Stream(DEV)
+    monkeypatch.setenv("PDA_PREFILL_IMAGE_MIN_TILES", "0")  # the image, where there is room for it
     monkeypatch.setenv("PDA_PREFILL_IMAGE_MAX_MB", "0")
     with torch.cuda.stream(s):
         call(out_g)  # sizes this stream's workspace for the staging path only
