@@ -406,7 +406,7 @@ def _prepare(q, k_cache, v_cache, block_table, seq_lens, kv_scales, out, max_seq
     prob = problem_for(q, k_cache, v_cache, block_table, seq_lens, max_seq_len, out)
     if kv_scales is not None and kv_scales.shape != (2, prob.num_blocks, prob.num_kv_heads):
         raise ValueError("kv_scales must be [2, num_blocks, num_kv_heads]")
-    if variant == "auto" and not (waves_per_cu or min_blocks_per_wave or chunks_per_wave or min_blocks_per_chunk):
+    if variant == "auto" and waves_per_cu == min_blocks_per_wave == chunks_per_wave == min_blocks_per_chunk == 0:
         return prob, None, index
     return prob, make_options(variant, waves_per_cu, min_blocks_per_wave, chunks_per_wave,
                               min_blocks_per_chunk), index
