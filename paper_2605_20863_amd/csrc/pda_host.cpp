@@ -411,11 +411,22 @@ int query_plan(const pda_problem* problem, const pda_options* options, float sof
 // 64 tokens 17.1 against 4.2, of 12,000 38.4 / 17.5; 32 units of 1,000 tokens
 // 20.3 / 10.9, of 12,000 54.7 / 47.6; 64 units of 1,000 21.3 / 13.0, of 3,000
 // 32.0 / 26.5, of 12,000 84.5 / 87.2; 128 units of 300 19.5 / 13.1, of 1,000
-// 25.9 / 28.1, of 3,000 47.4 / 71.2. The first bound is on the steps a wave
-// runs one after the other when one sequence has the longest length (12 at 256
-// compute units; half the length for the two-tile body and for f32 caches, whose
-// steps take about twice as long per token), the second on the work in flight,
-// which grows with units and length.
+// 25.9 / 28.1, of 3,000 47.4 / 71.2. The first bound is on units times length
+// (half of it for the two-tile body and for f32 caches, whose steps take about
+// twice as long per token), the second on the work in flight, which grows with
+// units and length. With at most kShortParts parts, few units leave compute units
+// idle and a wave with many steps, and are ahead all the same, as far as the first
+// bound goes (every length the same, stream-K / short): 1 unit of 16,384 tokens
+// 39.2 / 17.0, of 98,304 157.9 / 50.5, of 393,216 216 / 175 (f32 246 / 192; 4 query
+// tokens 226 / 174); 2 units of 196,608 130 / 96, 4 of 98,304 85 / 57.
+// With more units, parts are a whole number, and cus / units between two of them
+// makes a wave's steps more than the first bound says: the third bound is on the
+// steps that a wave of the longest length runs one after the other. One sequence
+// of the longest length beside others of a sixteenth: 96 units (2 parts) of 3,184
+// tokens, 13 steps, 23.5 / 27.4 (fp8 20.8 / 19.0); 80 (3 parts) of 4,576, 12 steps,
+// 24.1 / 26.4; f32, 96 of 2,048, 16 steps, 26.4 / 29.8;
+// 64 units of 6,144, 12 steps, 27.1 / 26.6; 128 of 1,792, 7 steps, 20.6 / 17.4;
+// 4 query tokens, 96 units of 2,048, 8 steps, 24.4 / 21.6.
 int short_parts(const pda_problem* pr, const Plan& plan, const Groups& gr, const pda_options* op, int cus,
                 int chunks_max) {
   // f32 caches and the MFMA body; options that ask for a split mean the stream's
@@ -429,10 +440,14 @@ int short_parts(const pda_problem* pr, const Plan& plan, const Groups& gr, const
   // one workgroup per compute unit (more gained nothing), a group of steps each at least
   const int64_t step = plan.kv == pda::KvType::F32 ? 16 : 32;
   const int64_t groups = (plan.len_cap + step * pda::kShortGroup - 1) / (step * pda::kShortGroup);
+  const int64_t most = wide ? pda::kShortParts / 2 : pda::kShortParts;
   int64_t parts = cus / units;
-  if (parts > (wide ? pda::kShortParts / 2 : pda::kShortParts)) parts = wide ? pda::kShortParts / 2 : pda::kShortParts;
+  if (parts > most) parts = most;
   if (parts > groups) parts = groups;
   if (parts < 1) parts = 1;
+  const int64_t steps = (groups + parts - 1) / parts;
+  const int64_t steps_max = wide ? 8 : plan.kv == pda::KvType::F32 ? 13 : plan.kv == pda::KvType::FP8 ? 16 : parts > 3 ? 12 : 9;
+  if (parts < most && steps > steps_max) return 0;
   return units * parts <= units + chunks_max ? (int)parts : 0;  // the layout's partial slots
 }
 

@@ -97,3 +97,15 @@ def test_the_fixed_scratch_clears_at_every_call(sim):
         sim.reset(capture=capture)
         rc, n = sim.decode(**SHORT, noalloc=True)
         assert rc == 0 and n["parts"] > 1 and n["clear"] == 1 and n["epoch"] == 0
+
+
+@pytest.mark.parametrize("kv,units,tokens,short", [
+    # (sequence, KV head) units of 4 KV heads; 2 parts each at 96: the longest a wave may run
+    (_lib.BF16, 96, 9 * 256, True), (_lib.BF16, 96, 9 * 256 + 16, False), (_lib.BF16, 96, 3184, False),
+    (_lib.FP8_E4M3, 96, 3184, True), (_lib.BF16, 80, 4576, False), (_lib.BF16, 64, 6144, True), (_lib.BF16, 128, 1792, True),
+    # one unit a sequence and head of few: up to the bound on units times length
+    (_lib.BF16, 4, 98304, True), (_lib.BF16, 4, 98304 + 16, False), (_lib.BF16, 192, 784, True), (_lib.BF16, 196, 64, False)])
+def test_short_decode_rule(sim, kv, units, tokens, short):
+    sim.reset()
+    rc, n = sim.decode(units // 4, 28, 4, 128, kv, blocks=tokens // 16)
+    assert rc == 0 and (n["parts"] > 0) == short
