@@ -409,7 +409,7 @@ int query_plan(const pda_problem* problem, const pda_options* options, float sof
 // evenly, were not yet ahead on lognormal lengths (sigma 0.5, the bound at the
 // longest; us per call, stream-K against short, bf16, 28 / 4 heads): 4 units of
 // 64 tokens 17.1 against 4.2, of 12,000 38.4 / 17.5; 32 units of 1,000 tokens
-// 20.3 / 10.9, of 12,000 54.7 / 47.6; 64 units of 1,000 21.3 / 13.0, of 3,000
+// 20.3 / 9.1, of 12,000 54.7 / 47.6; 64 units of 1,000 21.3 / 10.4, of 3,000
 // 32.0 / 26.5, of 12,000 84.5 / 87.2; 128 units of 300 19.5 / 13.1, of 1,000
 // 25.9 / 28.1, of 3,000 47.4 / 71.2. The first bound is on units times length
 // (half of it for the two-tile body and for f32 caches, whose steps take about
@@ -424,9 +424,9 @@ int query_plan(const pda_problem* problem, const pda_options* options, float sof
 // steps that a wave of the longest length runs one after the other. One sequence
 // of the longest length beside others of a sixteenth: 96 units (2 parts) of 3,184
 // tokens, 13 steps, 23.5 / 27.4 (fp8 20.8 / 19.0); 80 (3 parts) of 4,576, 12 steps,
-// 24.1 / 26.4; f32, 96 of 2,048, 16 steps, 26.4 / 29.8;
-// 64 units of 6,144, 12 steps, 27.1 / 26.6; 128 of 1,792, 7 steps, 20.6 / 17.4;
-// 4 query tokens, 96 units of 2,048, 8 steps, 24.4 / 21.6.
+// 24.1 / 26.4; f32, 96 of 2,048, 16 steps, 26.4 / 29.8; 64 units of 6,144, 12 steps,
+// 27.1 / 26.6; 128 of 1,792, 7 steps, 20.6 / 17.4; 4 query tokens, 96 units of
+// 2,048, 8 steps, 24.4 / 21.6.
 int short_parts(const pda_problem* pr, const Plan& plan, const Groups& gr, const pda_options* op, int cus,
                 int chunks_max) {
   // f32 caches and the MFMA body; options that ask for a split mean the stream's

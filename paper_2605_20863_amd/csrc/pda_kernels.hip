@@ -1467,8 +1467,8 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(DecodeArgs a) 
 // buffers with a body each cost 0.3-0.5 us per call, eight instead of four
 // partials per merge step 0.4, integer divisions by runtime values 0.6.
 // Measured, bf16, 28 / 4 heads, us per call in a HIP graph, stream-K -> here: one
-// sequence of 64 tokens 17.1 -> 4.2, 8 of about 1,000 20.3 -> 10.9, 16 of about
-// 1,000 21.3 -> 13.0.
+// sequence of 64 tokens 17.1 -> 4.2, 8 of about 1,000 20.3 -> 9.1, 16 of about
+// 1,000 21.3 -> 10.4.
 //
 // Parts cross XCDs, whose L2s are separate: partials are stored and loaded at
 // agent scope (write-through and past the L2), each workgroup waits for its

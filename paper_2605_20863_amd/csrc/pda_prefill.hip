@@ -17,13 +17,17 @@
 //   every tile of a block that a sequence with queries reads, converted to the
 //   operand types of the products (V to fp16, fp8 as code times the block's V
 //   scale; for fp8 caches K codes to bf16), indexed like the cache.
+//   In a mixed call (long prompts beside sequences of few tiles) only the
+//   former's blocks are written, and the work list is two: one for an attention
+//   launch that reads the image, one for another that reads the cache.
 // * Split plan. Where the tiles alone leave compute units idle (a chunk of one
 //   long prompt: 15 tiles x 4 KV heads on 256 CUs, each walking 16k keys), the
 //   plan cuts a tile's keys into several items; each writes its unnormalised
 //   output and softmax state, and a merge kernel combines them. Measured, 512
 //   tokens over 16,182 cached ones, 28 / 4 heads, bf16: 462 us per call whole,
-//   146 us split (prep 9, attention 120, merge 8); 64-token turns of 16
-//   sequences over an fp8 cache, 32 / 8 heads: 234 against 178.
+//   146 us split (alone, under the profiler: prep 11, attention 145, merge 8);
+//   64-token turns of 16 sequences over an fp8 cache, 32 / 8 heads: 234 against
+//   178, and 115 with the tiles read from the cache.
 // * Attention kernel: a persistent grid, one workgroup (8 waves, 2 per SIMD)
 //   per CU, that takes (item, KV head) units from queues, so a CU goes from one
 //   unit to the next without a workgroup launch between them (which cost ~4 us
@@ -1032,7 +1036,8 @@ __device__ __forceinline__ void pf_pv(PfOps<KV, D>& o, const f16x8 (&ph)[kPfNT],
 // The attention kernel's two instances per cache type, head size and tile
 // source: every item a whole tile, or items that may hold part of a tile's keys.
 // (One kernel template: a shared device function called from two kernels
-// compiled to other code, 2-3% slower for fp8 caches.)
+// compiled to other code, 2-3% slower for fp8 caches. The tags' names are part of
+// the kernels' symbols, by which the tests of their assembly find them.)
 struct whole_prefill_kernel {
   static constexpr bool kSplit = false;
 };
