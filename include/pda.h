@@ -384,13 +384,15 @@ typedef struct pda_prefill_problem {
  * accumulated in fp32. A live V value beyond +-65504 saturates (status bit 16).
  *
  * Image: a call of 5 or more query tiles (of 256 / G tokens) per sequence on
- * average, 8 for an fp8 cache (PDA_PREFILL_IMAGE_MIN_TILES in the environment,
+ * average, 8 for an fp8 cache (10 and 13 where max_seq_len, or the block table,
+ * bounds the lengths by 1,024; PDA_PREFILL_IMAGE_MIN_TILES in the environment,
  * read on every call, sets another number) first converts every cache tile that its sequences read
  * into the stream's workspace, in the products' operand types (V to fp16, and
  * for an fp8 cache K codes to bf16), indexed like the cache; the attention
  * kernel then copies tiles from that image straight into LDS. A call of fewer
- * on average but 100 or more (and twice that number) in all does so for those of
- * its sequences that have that many themselves. The image takes
+ * on average but 100 or more (and twice that number) in all, and lengths not
+ * bounded by 1,024, does so for those of its sequences that have that many
+ * themselves, or at most 64 keys. The image takes
  * num_blocks * num_kv_heads * 16 * head_dim * 2 bytes (twice that for an fp8
  * cache). With fewer tiles, when the image exceeds the environment variable
  * PDA_PREFILL_IMAGE_MAX_MB (MiB, read on every call; default 8192), when a

@@ -455,7 +455,8 @@ def paged_prefill_attention(q, q_offsets, k_cache, v_cache, block_table, seq_len
     q_offsets[b] .. q_offsets[b + 1] - 1 (int32 [B + 1]) are the last tokens of
     sequence b, whose cache holds seq_lens[b] tokens; cache layouts as for
     paged_decode_attention. A call of at least PDA_PREFILL_IMAGE_MIN_TILES
-    (default 5, 8 for fp8) tiles of 256 / G query tokens per sequence on average converts
+    (default 5, 8 for fp8; 10 and 13 for lengths bounded by 1,024) tiles of 256 / G
+    query tokens per sequence on average converts
     the cache tiles it reads into an image in the stream's workspace (V as fp16,
     an fp8 cache's K as bf16; NB * Hkv * 16 * D * 2 bytes, twice that for fp8)
     unless that exceeds PDA_PREFILL_IMAGE_MAX_MB (default 8192); with fewer on

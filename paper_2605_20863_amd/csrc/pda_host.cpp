@@ -676,8 +676,9 @@ int64_t prefill_image_cap() {
 // Query tiles per sequence (the call's average) from which a prefill writes
 // the image: PDA_PREFILL_IMAGE_MIN_TILES (read on each call; 0 writes it
 // whenever it fits), by default where both ways take the same time.
-int64_t prefill_image_tiles(bool fp8) {
-  const int by_default = fp8 ? pda::kPfImageTilesFp8 : pda::kPfImageTilesBf16;
+int64_t prefill_image_tiles(bool fp8, int len_cap) {
+  const int by_default = len_cap > pda::kPfImageKeys ? (fp8 ? pda::kPfImageTilesFp8 : pda::kPfImageTilesBf16)
+                                                     : (fp8 ? pda::kPfImageTilesShortFp8 : pda::kPfImageTilesShortBf16);
   const char* v = std::getenv("PDA_PREFILL_IMAGE_MIN_TILES");
   if (!v || !*v) return by_default;
   char* end = nullptr;
@@ -784,18 +785,23 @@ int prefill_run(const void* q, const int32_t* q_offsets, const void* k_cache, co
   //                             n = 8 294 / 303; 322 / 319
   //   32 / 8 heads, 32 x 2,048: n = 2 207 / 183; 250 / 189   n = 5 403 / 398; 450 / 405
   //                             n = 8 544 / 559; 588 / 595   n = 16 897 / 963; 944 / 1,025
+  //                 64 x   600: n = 5 273 / 261; 300 / 275   n = 9 380 / 374; 411 / 394
+  // (short sequences' images cost the same per key and are read for fewer pairs).
   //
   // The average says too little where a batch mixes long prompts with one-token
   // rows or empty slots. With fewer tiles per sequence on average, but many in
-  // all, the call is mixed: the plan decides sequence by sequence. That is a
+  // all and room for long sequences, the call is mixed: the plan decides
+  // sequence by sequence. That is a
   // second attention launch, 3 us if its list is empty and 10 to 25 with a few
   // short items, for about 10% of the prompts' time: from 100 tiles on. One
-  // prompt of 8,192 beside 31 rows of one token each, converting / mixed: 28 / 4
-  // heads bf16 543 / 489, fp8 581 / 524; beside 31 rows over 2,048 tokens 582 / 542,
-  // 620 / 574. One of 2,048 (57 tiles) beside 31 rows: 94 / 98.
-  const int64_t tiles_min = prefill_image_tiles(kd == PDA_DTYPE_FP8_E4M3), tiles_all = pr->num_tokens / TQ;
+  // prompt of 8,192 beside 31 rows of one key each, converting / mixed: 28 / 4
+  // heads bf16 546 / 483, fp8 577 / 514; beside 31 rows over 256 keys 547 / 507,
+  // 579 / 527; over 2,048 582 / 542, 620 / 574. One of 2,048 (57 tiles) beside 31
+  // rows: 94 / 98. Rows of up to kPfMixedKeys keys go with the image (31 of one
+  // key 489 / 483), no longer ones (127 of 100 keys 540 there, 506 from the cache).
+  const int64_t tiles_min = prefill_image_tiles(kd == PDA_DTYPE_FP8_E4M3, len_cap), tiles_all = pr->num_tokens / TQ;
   const bool mixed = tiles_all < tiles_min * pr->num_seqs;
-  bool use_img = img_bytes <= prefill_image_cap() && (!mixed || (tiles_all >= pda::kPfMixedTiles && tiles_all >= 2 * tiles_min));
+  bool use_img = img_bytes <= prefill_image_cap() && (!mixed || (tiles_all >= pda::kPfMixedTiles && tiles_all >= 2 * tiles_min && len_cap > pda::kPfImageKeys));
   struct PrefillLayout {
     int64_t list_max, parts, splits, ml, acc, img, total;
   };

@@ -145,9 +145,13 @@ constexpr int kPfBuckets = 2048; // length classes of the plan's counting sort
 constexpr int kPfSplitUnits = 8;
 constexpr int kPfSplitTiles = 2048;
 constexpr int kPfSplitSeqs = 1024;
-// query tiles per sequence (the call's average) from which the image is written
+// query tiles per sequence (the call's average) from which the image is written,
+// for sequences of more than kPfImageKeys keys and for shorter ones
+constexpr int kPfImageKeys = 1024;
 constexpr int kPfImageTilesBf16 = 5, kPfImageTilesFp8 = 8;
+constexpr int kPfImageTilesShortBf16 = 10, kPfImageTilesShortFp8 = 13;
 constexpr int kPfMixedTiles = 100;  // fewest query tiles of a mixed call
+constexpr int kPfMixedKeys = 64;   // a mixed call's sequences of at most this many keys are in the image
 constexpr int kPfSplitPairs = 16;  // fewest 32-key pairs a split makes per item
 
 struct PrefillArgs {
@@ -174,8 +178,8 @@ struct PrefillArgs {
   int32_t* hdr;         // workspace header (status, item count, queue counters)
   int4* items;          // [list_max] {sequence, first q row, tokens, first position}
   int32_t list_max;     // items_max + slots
-  // > 0 (mixed): only the sequences of at least this many query tiles have their
-  // tiles in the image; the others' items are a second list right behind the
+  // > 0 (mixed): only the sequences of at least this many query tiles, or at most
+  // kPfMixedKeys keys, have their tiles in the image; the others' items are a second list right behind the
   // first (and so are its parts), run by a launch of its own that reads the cache.
   int32_t img_tiles;
   // Image of the cache's tiles in the products' operand types, indexed like the

@@ -217,19 +217,24 @@ __device__ __forceinline__ void pf_bucket_starts(const PrefillArgs& a, PfPlanLds
 // 32-key pairs of `keys` keys
 __device__ __forceinline__ int pf_pairs(int keys) { return keys > 0 ? (keys + 31) / 32 : 0; }
 
-// Mixed calls have two lists, sorted as one: the items of the sequences with n
-// query tokens enough for the image, and behind them (in the upper half of the
-// buckets, in memory a.list_max entries on) the others'.
-__device__ __forceinline__ bool pf_staged(const PrefillArgs& a, int n) { return (n + a.TQ - 1) / a.TQ < a.img_tiles; }
+// Mixed calls have two lists, sorted as one: the items of the sequences whose
+// tiles are in the image, and behind them (in the upper half of the buckets, in
+// memory a.list_max entries on) the others'. In the image are the sequences with
+// tiles enough, and those whose few keys cost next to nothing to convert: with
+// nothing but one-token rows of short sequences beside the prompts, the second
+// launch has an empty list.
+__device__ __forceinline__ bool pf_staged(const PrefillArgs& a, int n, int L) {
+  return (n + a.TQ - 1) / a.TQ < a.img_tiles && L > kPfMixedKeys;
+}
 
-__device__ __forceinline__ int pf_bucket(const PrefillArgs& a, int key, int n) {
-  return a.img_tiles > 0 ? key / 2 + (pf_staged(a, n) ? kPfBuckets / 2 : 0) : key;
+__device__ __forceinline__ int pf_bucket(const PrefillArgs& a, int key, int n, int L) {
+  return a.img_tiles > 0 ? key / 2 + (pf_staged(a, n, L) ? kPfBuckets / 2 : 0) : key;
 }
 
 // Place in memory of the item at `pos` of the sorted list, of a sequence of n
-// query tokens.
-__device__ __forceinline__ int pf_place(const PrefillArgs& a, const PfPlanLds& s, int pos, int n) {
-  return a.img_tiles > 0 && pf_staged(a, n) ? pos - s.imaged + a.list_max : pos;
+// query tokens and L keys.
+__device__ __forceinline__ int pf_place(const PrefillArgs& a, const PfPlanLds& s, int pos, int n, int L) {
+  return a.img_tiles > 0 && pf_staged(a, n, L) ? pos - s.imaged + a.list_max : pos;
 }
 
 // Offsets that are not non-decreasing within [0, T] list no item at all (status
@@ -242,7 +247,7 @@ __device__ void pf_plan_tiles(const PrefillArgs& a, PfPlanLds& lds) {
   bool bad = false;
   for (int b = tid; b < a.B; b += kPlanThreads) {
     const PfSeq s = pf_seq(a, b, status, bad);
-    if (s.tiles) atomicAdd(&cursor[pf_bucket(a, s.key, s.n)], s.tiles);
+    if (s.tiles) atomicAdd(&cursor[pf_bucket(a, s.key, s.n, s.L)], s.tiles);
   }
   if (__syncthreads_or(bad)) {
     if (tid == 0) {
@@ -255,7 +260,7 @@ __device__ void pf_plan_tiles(const PrefillArgs& a, PfPlanLds& lds) {
   for (int b = tid; b < a.B; b += kPlanThreads) {
     const PfSeq s = pf_seq(a, b, status, bad);
     if (!s.tiles) continue;
-    int pos = pf_place(a, lds, atomicAdd(&cursor[pf_bucket(a, s.key, s.n)], s.tiles), s.n);
+    int pos = pf_place(a, lds, atomicAdd(&cursor[pf_bucket(a, s.key, s.n, s.L)], s.tiles), s.n, s.L);
     for (int t = s.tiles - 1; t >= 0; --t) {  // the last (heaviest) tile first
       const int t0 = t * a.TQ;
       const int nt = s.n - t0 < a.TQ ? s.n - t0 : a.TQ;
@@ -398,7 +403,8 @@ __device__ void pf_plan_split(const PrefillArgs& a, PfSplitLds& lds) {
   for (int i = tid; i < tiles; i += kPlanThreads) {
     int len;
     const int c = cut(lds.tile_p[i], len);
-    atomicAdd(&lds.cursor[pf_bucket(a, key(len), lds.n[lds.tile_b[i]])], c);
+    const int b = lds.tile_b[i];
+    atomicAdd(&lds.cursor[pf_bucket(a, key(len), lds.n[b], lds.L[b])], c);
   }
   __syncthreads();
   pf_bucket_starts(a, lds);
@@ -408,7 +414,8 @@ __device__ void pf_plan_split(const PrefillArgs& a, PfSplitLds& lds) {
     const int nt = n - t0 < a.TQ ? n - t0 : a.TQ;
     int len;
     const int c = cut(p, len);
-    int pos = pf_place(a, lds, atomicAdd(&lds.cursor[pf_bucket(a, key(len), n)], c), n);
+    const int L = lds.L[b];
+    int pos = pf_place(a, lds, atomicAdd(&lds.cursor[pf_bucket(a, key(len), n, L)], c), n, L);
     int slot = -1;
     if (c > 1) {
       slot = atomicAdd(&lds.nslots, c);
@@ -416,7 +423,7 @@ __device__ void pf_plan_split(const PrefillArgs& a, PfSplitLds& lds) {
     }
     for (int j = 0; j < c; ++j, ++pos) {
       const int end = (j + 1) * len;
-      a.items[pos] = make_int4(b, row0, nt, lds.L[b] - n + t0);
+      a.items[pos] = make_int4(b, row0, nt, L - n + t0);
       a.parts[pos] = make_int4(j * len, end < p ? end : p, slot < 0 ? -1 : slot + j, 0);
     }
   }
@@ -557,9 +564,9 @@ __device__ void pf_image(const PrefillArgs& a, int g) {
   const int j0 = (g - b * cps) << a.img_shift;
   const int o0 = a.q_offsets[b], o1 = a.q_offsets[b + 1];
   if (o0 < 0 || o1 > a.T || o1 <= o0) return;  // no queries, or offsets the plan rejects
-  if (a.img_tiles > 0 && pf_staged(a, o1 - o0)) return;
   int L = a.seq_lens[b];
   L = L < 0 ? 0 : (L > a.len_cap ? a.len_cap : L);
+  if (a.img_tiles > 0 && pf_staged(a, o1 - o0, L)) return;
   const int nblk = (L + 15) / 16;
   const int nb = nblk - j0 < blocks ? nblk - j0 : blocks;
   if (nb <= 0) return;

@@ -32,9 +32,17 @@ def fresh(sim, monkeypatch):
     # too few tiles for the second launch to pay
     (32, 6000, BF16, False, 0), (64, 64 * 64, FP8, False, 0)])
 def test_image_rule(sim, B, tokens, kv, image, mixed):
-    rc, n = sim.prefill(B, tokens, 32, 8, 128, kv, 512)
+    rc, n = sim.prefill(B, tokens, 32, 8, 128, kv, 512)  # up to 8,192 keys
     assert rc == 0 and bool(n["v_img"]) == image and n["img_tiles"] == mixed
     assert bool(n["k_img"]) == (image and kv == FP8)
+
+
+@pytest.mark.parametrize("tiles,kv,blocks,image", [
+    (9, BF16, 64, False), (10, BF16, 64, True), (9, BF16, 65, True), (12, FP8, 64, False), (13, FP8, 64, True),
+    (12, FP8, 65, True)])
+def test_image_rule_of_short_sequences(sim, tiles, kv, blocks, image):
+    rc, n = sim.prefill(16, 16 * 64 * tiles, 32, 8, 128, kv, blocks)
+    assert rc == 0 and bool(n["v_img"]) == image and n["img_tiles"] == 0  # and none is mixed
 
 
 CALL = dict(B=4, T=4 * 700, hq=28, hkv=4, d=128, kv=BF16, blocks=2048)
@@ -94,7 +102,7 @@ def test_a_capture_without_room_goes_without(sim, monkeypatch, call):
 
 def test_nothing_overlaps_in_the_workspace(sim):
     """Lists, parts, splits, partials and image, in order and inside the allocation."""
-    for call in (CALL, MIXED, {**CALL, "kv": FP8}, {**MIXED, "B": 1200, "T": 20000, "blocks": 32}):
+    for call in (CALL, MIXED, {**CALL, "kv": FP8}, {**MIXED, "B": 1200, "T": 20000, "blocks": 65}):
         sim.release()
         rc, n = sim.prefill(**call)
         assert rc == 0 and n["v_img"]
